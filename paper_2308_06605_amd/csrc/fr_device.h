@@ -18,10 +18,12 @@ struct Phys {
   real gamma, gm1, mu, kappa;
 };
 
+// a.b in one order of rounding. Written as a sum of products, which product is fused with the
+// additions depends on the code around it, and kernels that share an expression (the volume
+// kernel with and without the next stage's pre-pass) could then differ in the last place.
 template <typename real>
-__device__ __forceinline__ real pressure(const real U[5], real gm1) {
-  const real ir = real(1) / U[0];
-  return gm1 * (U[4] - real(0.5) * (U[1] * U[1] + U[2] * U[2] + U[3] * U[3]) * ir);
+__device__ __forceinline__ real dot3(real a0, real b0, real a1, real b1, real a2, real b2) {
+  return fma(a2, b2, fma(a0, b0, a1 * b1));
 }
 
 // Inviscid flux along a unit or scaled direction n: F(U).n, plus u.n and c.
@@ -30,8 +32,8 @@ __device__ __forceinline__ void flux_n(const real U[5], const real n[3], const P
                                        real &un, real &c) {
   const real ir = real(1) / U[0];
   const real u = U[1] * ir, v = U[2] * ir, w = U[3] * ir;
-  const real p = ph.gm1 * (U[4] - real(0.5) * U[0] * (u * u + v * v + w * w));
-  un = u * n[0] + v * n[1] + w * n[2];
+  const real p = ph.gm1 * (U[4] - real(0.5) * U[0] * dot3(u, u, v, v, w, w));
+  un = dot3(u, n[0], v, n[1], w, n[2]);
   F[0] = U[0] * un;
   F[1] = U[1] * un + p * n[0];
   F[2] = U[2] * un + p * n[1];
@@ -113,7 +115,7 @@ __device__ __forceinline__ void visc_flux_mk(const real U[5], const real G[3][5]
 #pragma unroll
     for (int j = 0; j < 3; ++j) du[i][j] = (G[i][1 + j] - u[j] * G[i][0]) * ir;
     const real de = (G[i][4] - e * G[i][0]) * ir;
-    dT[i] = gm1 * (de - (u[0] * du[i][0] + u[1] * du[i][1] + u[2] * du[i][2]));
+    dT[i] = gm1 * (de - dot3(u[0], du[i][0], u[1], du[i][1], u[2], du[i][2]));
   }
   const real lam = real(-2.0 / 3.0) * mu * (du[0][0] + du[1][1] + du[2][2]);
 #pragma unroll
@@ -144,7 +146,7 @@ __device__ __forceinline__ void visc_flux(const real U[5], const real G[3][5], c
 __device__ __forceinline__ double body_force(const StageArgs &st, const double X[5], int v) {
   if (!st.force || v == 0) return 0.0;
   if (v < 4) return X[0] * st.g[v - 1];
-  return X[1] * st.g[0] + X[2] * st.g[1] + X[3] * st.g[2];
+  return dot3(X[1], st.g[0], X[2], st.g[1], X[3], st.g[2]);
 }
 
 // x: the state the stage was evaluated on; R: its residual; r1, r2: the registers' old values.
@@ -163,33 +165,33 @@ __device__ __forceinline__ double rk_store(const StageArgs &st, int64_t o, doubl
     return 0.0;
   }
   if (st.mode == kModeLSRK) {
-    const double du = st.a * r1 + st.dt * R;
-    const double u = x + st.b * du;
+    const double du = fma(st.a, r1, st.dt * R);
+    const double u = fma(st.b, du, x);
     reg1[o] = du;
     out0[o] = u;
     return u;
   }
   if (st.mode == kModeRK4) {
-    const double acc = r1 + st.w * R;
+    const double acc = fma(st.w, R, r1);
     if (!st.last) {
-      const double sn = r2 + st.cdt * R;
+      const double sn = fma(st.cdt, R, r2);
       reg1[o] = acc;
       reg2[o] = sn;
       return sn;
     }
-    const double q = r2 + st.dt * acc;
+    const double q = fma(st.dt, acc, r2);
     out0[o] = q;
     return q;
   }
   if (st.stage == 9) {
-    const double q = r1 + 0.6 * x + st.dt / 10 * R;
+    const double q = fma(st.dt / 10, R, fma(0.6, x, r1));
     out0[o] = q;
     return q;
   }
-  const double q1 = x + st.dt / 6 * R;
+  const double q1 = fma(st.dt / 6, R, x);
   if (st.stage == 4) {
-    const double q2 = r1 / 25 + 9.0 / 25 * q1;
-    const double q = 15 * q2 - 5 * q1;
+    const double q2 = fma(9.0 / 25, q1, r1 / 25);
+    const double q = fma(15.0, q2, -5 * q1);
     reg1[o] = q2;
     out0[o] = q;
     return q;
@@ -216,12 +218,12 @@ struct Cfg {
   static constexpr int EPB2 = EPB > 1 ? EPB / 2 : (NS % 64 != 0 && 2 * NS <= 1024 ? 2 : 1);
 };
 
-// Occupancy targets (waves per SIMD) per kernel and degree; 0 lets the compiler decide.
-// The volume kernel without the closure asks for 4 at p = 3 and p = 7. At p = 3 the compiler's
-// own choice is 130 VGPRs (3 waves) and 128 fit without spilling (the kernel 7.5% faster at
-// 64^3); with the fused pre-pass (PRE) both degrees spill a few bytes per lane at 4 waves and
-// are still faster than at the compiler's 2-3 waves (measured at 64^3 p=3 and 32^3 p=7).
-// Elsewhere forcing more waves than the compiler picks spilled more and ran slower.
+// Occupancy targets (waves per SIMD) per kernel and degree; 0 lets the compiler decide. From
+// p = 2 on the FP64 volume kernels ask for 4 (at most 128 VGPRs): left alone the compiler takes
+// up to 165 (3 waves; 2 for some) to hoist LDS reads, and the kernels are short of waves, not of
+// loads in flight. They fit without spills, but for 12 bytes per lane at p = 3 and 20 to 28 at
+// p = 6 in the instances without the fused pre-pass. The FP32 form's volume kernel asks for 4
+// at p = 5 and p = 7 and takes about 100 VGPRs at every degree.
 #ifndef FR_WPE_PREPASS
 #define FR_WPE_PREPASS(P) 0
 #endif
@@ -229,42 +231,10 @@ struct Cfg {
 #define FR_WPE_FACE(P) 0
 #endif
 #ifndef FR_WPE_VOLUME
-#define FR_WPE_VOLUME(P, SGS, PRE) (((P) == 3 || (P) == 7) && !(SGS) ? 4 : 0)
+#define FR_WPE_VOLUME(P, SGS, PRE) ((P) >= 2 ? 4 : 0)
 #endif
-// The FP32 form's volume kernel asks for 4 at p = 5 and p = 7. At p = 7 the compiler's choice
-// is 130 VGPRs and 128 fit without spill; at p = 5 it is 132 (3 waves), and at 128 the fused
-// instance spills 4 bytes per lane and runs 10% faster (43^3 p=5: 2.23 -> 1.99 ms, same box).
-// At p = 2 and 4 the compiler already picks 4; the FP64 kernels at p = 4 and 5 lost 1-5% at 4.
 #ifndef FR_WPE_VOLUME32
 #define FR_WPE_VOLUME32(P) ((P) == 5 || (P) == 7 ? 4 : 0)
-#endif
-// How a single-pass fused tail spreads the face values over its threads. FP32 form: whole face
-// points per thread (each point's line and interpolation weights worked out once for all its
-// values) at the degrees listed, else (group, face point) items of five sums. FP64: items of
-// FR_TAIL_GROUPS64 of the four groups (4: whole face points). Measured per degree (A/B in one
-// call): whole points are faster at p = 2 (FP32 +13%, FP64 +5%; taken for p = 0, 1 too, where
-// the points also divide evenly over the threads), p = 4 (+1%, +2%) and at p = 5, 6 in the FP32
-// form (+3%, +1%), slower at p = 3 in FP64 (-10%; items of two groups were no faster than one,
-// 5.78-5.85e9 against 5.80-5.82e9, nor whole points after the operator reads moved to LDS and
-// scalar loads, 5.87e9 against 5.92e9) and at p = 5 in FP64 (-1%). In the FP32 form at p = 3
-// whole points were 2% slower at first and 6% faster after those changes (7.89e9 -> 8.36e9).
-#ifndef FR_TAIL_GROUPS64
-#define FR_TAIL_GROUPS64(P) ((P) <= 2 || (P) == 4 ? 4 : 1)
-#endif
-#ifndef FR_TAIL_PER_POINT32
-#define FR_TAIL_PER_POINT32(P) ((P) <= 6)
-#endif
-// Degrees at which the kernels make that choice from scalar loads (pick_end); elsewhere the
-// compiler's vector load of a selected address stays. Measured per degree (A/B in one call):
-// FP64 64^3 p=3 +1-2%, 52^3 p=4 +2.5%, 43^3 p=5 +4%, while at 80^3 p=2 the fused volume kernel
-// went from 1.99 to 2.09 ms and at 37^3 p=6 it took 130 VGPRs (a wave per SIMD less); FP32 form
-// 64^3 p=3 +3%, 52^3 p=4 +12%, 43^3 p=5 +11%, 37^3 p=6 +8%, 80^3 p=2 -3%. At p = 7 the choice
-// is made per wave (no difference).
-#ifndef FR_SCALAR_ENDS64
-#define FR_SCALAR_ENDS64(P) ((P) == 3 || (P) == 4 || (P) == 5)
-#endif
-#ifndef FR_SCALAR_ENDS32
-#define FR_SCALAR_ENDS32(P) ((P) >= 3)
 #endif
 #define FR_WPE_ATTR(w) __attribute__((amdgpu_waves_per_eu((w) > 0 ? (w) : 1, (w) > 0 ? 8 : 8)))
 
@@ -278,28 +248,6 @@ constexpr bool lds_copy_fits(int bytes, int extra, int threads) {
   return lds_blocks(bytes + extra, threads) == lds_blocks(bytes, threads);
 }
 
-// An operator entry at a uniform index, chosen per lane between two tables (the interpolation
-// to the face at -1 or at +1). As a select of the two values the compiler makes it one vector
-// load from a selected address, and a vector load completes only after every vector memory
-// access the wave issued before it (the RK-register loads, the stores of earlier face points).
-// Passing both through readfirstlane keeps them scalar loads and the choice a register select.
-template <typename T>
-__device__ __forceinline__ T uniform_value(T x) {
-  if constexpr (sizeof(T) == 8) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
-    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)b);
-    const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
-    return __builtin_bit_cast(T, ((unsigned long long)hi << 32) | lo);
-  } else {
-    return __builtin_bit_cast(T, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
-  }
-}
-template <bool SCALAR, typename T>
-__device__ __forceinline__ T pick_end(bool hi, const T *lm, const T *lp, int c) {
-  if constexpr (SCALAR) return hi ? uniform_value(lp[c]) : uniform_value(lm[c]);
-  else return hi ? lp[c] : lm[c];
-}
-
 template <typename real>
 struct OpsT {
   real D[kMaxN * kMaxN];
@@ -307,7 +255,37 @@ struct OpsT {
   real lp[kMaxN];
   real gcL[kMaxN];
   real gcR[kMaxN];
+  real W[kMaxN * kMaxN];
 };
+
+// Entry i of the operator entries a volume kernel keeps in LDS: D [N][N], gcL [N], gcR [N],
+// W [N][N] (kOpEntries of them).
+template <int N>
+constexpr int kOpEntries = 2 * N * N + 2 * N;
+template <int N, typename real>
+__device__ __forceinline__ real op_entry(const OpsT<real> &ops, int i) {
+  const real *tab = reinterpret_cast<const real *>(&ops);
+  constexpr int oL = kMaxN * kMaxN + 2 * kMaxN, oR = oL + kMaxN, oW = oR + kMaxN;
+  static_assert(sizeof(OpsT<real>) == (oW + kMaxN * kMaxN) * sizeof(real), "the table's members in order");
+  return tab[i < N * N ? i : (i < N * N + N ? oL + i - N * N : (i < N * N + 2 * N ? oR + i - N * N - N : oW + i - N * N - 2 * N))];
+}
+
+// Barrier between the LDS phases of an element's threads. Where an element's points fill whole
+// waves or a wave holds whole elements (N_s = 1, 8, 64), only lanes of one wave exchange data:
+// a wave's LDS instructions execute in order, so ordering the compiler's accesses is enough and
+// the block's waves run on independently. Otherwise a block barrier.
+template <int NS>
+constexpr bool kWaveElement = 64 % NS == 0;
+template <int NS>
+__device__ __forceinline__ void elem_sync() {
+  if constexpr (kWaveElement<NS>) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
 
 // Stores to the per-face-point buffers, which are written once and read once by the next
 // kernel, as runs of NFP entries per value. They are non-temporal (+2.8% per stage at 64^3
@@ -333,36 +311,35 @@ __device__ __forceinline__ int plane_index(int t) {
   else return t / (N * N);
 }
 
-// Face interpolation of a point-ordered element array src: the sum over the line normal to
-// face f (direction d = f/2) through its face point (a, b) of ell[c] src[line_pt(d, c, a, b)],
-// with ell = l(-1) or l(+1) by the face's side. f must be the same on every lane of the
-// wavefront (the p = 7 kernels give each wavefront one face of 64 points): the direction then
-// picks one of three loops whose LDS strides are constants.
-// * In ascending c (ROT false, and faces normal to xi_2 always) ell is read through scalar
-//   loads. On faces normal to xi_0 and xi_1 the lines' common stride (8 or 64 entries) then puts
-//   8 lanes of a wavefront on one LDS bank at every step (16 for doubles): an 8-way conflict.
-// * With ROT, a lane of a face normal to xi_0 reads its whole line (contiguous) with 16-byte
-//   loads, two for floats and four for doubles, and sums it in ascending c; src must then be
-//   16-byte aligned. On faces normal to xi_1 lane (a, b) starts at c = b and wraps around
-//   (mod 8): every step then reads 64 different banks for floats, and 32 different 8-byte bank
-//   pairs per half-wavefront for doubles. The weights of the rotated order come from rot, an
-//   LDS table [l(-1), l(-1), l(+1), l(+1)] (rot_entry) where they are contiguous.
-// A form's kernels all take the same ROT, so fused and separate stages keep the same sums. The
+// Interpolation to both faces normal to direction d: the sums over the line through their face
+// point (a, b) of lm[c] src[line_pt(d, c, a, b)] and lp[c] src[...], the line read once for the
+// two. d must be the same on every lane of the wavefront (the p = 7 kernels give each wavefront
+// one direction's 64 lines); it picks one of three loops whose LDS strides are constants.
+// * In ascending c (ROT false, and d = 2 always) lm and lp are read through scalar loads. For
+//   d = 0 and 1 the lines' common stride (8 or 64 entries) then puts 8 lanes of a wavefront on
+//   one LDS bank at every step (16 for doubles): an 8-way conflict.
+// * With ROT, a lane of d = 0 reads its whole line (contiguous) with 16-byte loads, two for
+//   floats and four for doubles, and sums it in ascending c; src must then be 16-byte aligned.
+//   For d = 1 lane (a, b) starts at c = b and wraps around (mod 8): every step then reads 64
+//   different banks for floats, and 32 different 8-byte bank pairs per half-wavefront for
+//   doubles. The weights of the rotated order come from rot, an LDS table [l(-1), l(-1), l(+1),
+//   l(+1)] (rot_entry) where they are contiguous.
+// A form's kernels all take the same ROT, and the sums are written with fma (left to the
+// compiler, a sum whose last addition is moved behind a branch stays unfused in one kernel and not
+// in another), so fused and separate stages keep the same sums. The
 // FP32 form's p = 7 kernels take it (32^3: the pre-pass, at 6.5 conflict cycles per LDS
-// instruction, went from 0.66 to 0.56 ms); the FP64 ones do not: there the rotated sums cost
-// the fused volume kernel more than they saved (1.74 -> 1.80 ms), and their table would cost
-// the pre-pass, whose two blocks fill the LDS exactly, one of them.
+// instruction, went from 0.66 to 0.56 ms with one face per task); the FP64 ones do not: there the
+// rotated sums cost the fused volume kernel more than they saved (1.74 -> 1.80 ms), and their
+// table would cost the pre-pass, whose two blocks fill the LDS exactly, one of them.
 template <int N, typename C>
 __device__ __forceinline__ C rot_entry(const C *lm, const C *lp, int i) {
   return i < 2 * N ? lm[i % N] : lp[i % N];
 }
 template <int N, bool ROT = false, typename T, typename C>
-__device__ __forceinline__ T face_sum_uniform(int f, int a, int b, const T *src, const C *lm, const C *lp,
-                                              const C *rot = nullptr) {
+__device__ __forceinline__ void face_sums_uniform(int d, int a, int b, const T *src, const C *lm, const C *lp, T &lo,
+                                                  T &hi, const C *rot = nullptr) {
   constexpr bool R = ROT && N == 8;  // the rotation is worked out for lines of eight points
-  const C *ell = (f & 1) ? lp : lm;
-  const int d = f >> 1;
-  T acc = 0;
+  lo = hi = 0;
   if (R && d == 0) {
     constexpr int K = 16 / (int)sizeof(T);
     using V = T __attribute__((ext_vector_type(K)));
@@ -371,28 +348,46 @@ __device__ __forceinline__ T face_sum_uniform(int f, int a, int b, const T *src,
     for (int j = 0; j < N / K; ++j) {
       const V x = q[j];
 #pragma unroll
-      for (int k = 0; k < K; ++k) acc += ell[j * K + k] * x[k];
+      for (int k = 0; k < K; ++k) {
+        lo = fma(lm[j * K + k], x[k], lo);
+        hi = fma(lp[j * K + k], x[k], hi);
+      }
     }
   } else if (R && d == 1) {
     const int r = b & (N - 1);
-    const C *w = rot + ((f & 1) ? 2 * N : 0) + r;
+    const C *w = rot + r;
     const T *q = src + a + N * N * b;
 #pragma unroll
-    for (int s = 0; s < N; ++s) acc += w[s] * q[((s + r) & (N - 1)) * N];
-  } else if (d == 0) {
-    const T *q = src + N * (a + N * b);
-#pragma unroll
-    for (int c = 0; c < N; ++c) acc += ell[c] * q[c];
-  } else if (d == 1) {
-    const T *q = src + a + N * N * b;
-#pragma unroll
-    for (int c = 0; c < N; ++c) acc += ell[c] * q[c * N];
+    for (int s = 0; s < N; ++s) {
+      const T x = q[((s + r) & (N - 1)) * N];
+      lo = fma(w[s], x, lo);
+      hi = fma(w[2 * N + s], x, hi);
+    }
   } else {
-    const T *q = src + a + N * b;
+    const int base = d == 0 ? N * (a + N * b) : (d == 1 ? a + N * N * b : a + N * b);
+    if (d == 0) {
 #pragma unroll
-    for (int c = 0; c < N; ++c) acc += ell[c] * q[c * N * N];
+      for (int c = 0; c < N; ++c) {
+        const T x = src[base + c];
+        lo = fma(lm[c], x, lo);
+        hi = fma(lp[c], x, hi);
+      }
+    } else if (d == 1) {
+#pragma unroll
+      for (int c = 0; c < N; ++c) {
+        const T x = src[base + c * N];
+        lo = fma(lm[c], x, lo);
+        hi = fma(lp[c], x, hi);
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < N; ++c) {
+        const T x = src[base + c * N * N];
+        lo = fma(lm[c], x, lo);
+        hi = fma(lp[c], x, hi);
+      }
+    }
   }
-  return acc;
 }
 
 // One wavefront per face of the element (64 face points, one per lane): p = 7 with one element
@@ -407,3 +402,38 @@ __device__ __forceinline__ int line_pt(int d, int c, int a, int b) {
   return d == 0 ? c + N * (a + N * b) : (d == 1 ? a + N * (c + N * b) : a + N * (b + N * c));
 }
 
+// The face values of NV point-ordered element arrays (array v at src + v N_s): every line of
+// points normal to a pair of faces is read once and gives the values at both its ends, with
+// uniform weights (scalar registers). Items are (GV arrays, line) over the element's threads t,
+// one direction after the other, so the line's LDS strides are constants and consecutive lanes
+// store consecutive points of a face. GV: few arrays per item where an item per line would leave
+// many threads idle (N^2 lines of NV / GV items over N^3 threads). dst: the element's first face
+// entry, [6][nval][NFP]; array v goes to its entry slot(v), which steps by one within an item.
+template <int N, int NV, int GV, typename T, typename C, typename Slot>
+__device__ __forceinline__ void write_traces(int t, const T *src, const C *lm, const C *lp, T *dst, int nval, Slot slot) {
+  constexpr int NFP = N * N, NS = N * N * N, ITEMS = NV / GV * NFP;
+  static_assert(NV % GV == 0, "arrays per item");
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    for (int q = t; q < ITEMS; q += NS) {
+      const int grp = q / NFP, kk = q - grp * NFP;
+      const T *x = src + grp * (GV * NS) + (d == 0 ? N * kk : (d == 1 ? kk % N + NFP * (kk / N) : kk));
+      T *out = dst + (2 * d * nval + slot(grp * GV)) * NFP + kk;
+#pragma unroll
+      for (int v = 0; v < GV; ++v) {
+        T lo = 0, hi = 0;
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+          const T y = x[v * NS + c * (d == 0 ? 1 : (d == 1 ? N : NFP))];
+          lo = fma(lm[c], y, lo);
+          hi = fma(lp[c], y, hi);
+        }
+        face_store<NFP>(lo, &out[v * NFP]);
+        face_store<NFP>(hi, &out[(nval + v) * NFP]);
+      }
+    }
+  }
+}
+// Arrays per item for 20 arrays: 5 where (20 / 5) N^2 items fill the N^3 threads, else 1.
+template <int N>
+constexpr int kTraceGroup = N == 1 || N == 2 || N == 4 ? 5 : 1;

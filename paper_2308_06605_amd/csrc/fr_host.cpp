@@ -522,6 +522,9 @@ Ops1D basis_ops(int p) {
     o.gcL[i] = (double)B.gcL[i];
     o.gcR[i] = (double)B.gcR[i];
   }
+  for (int a = 0; a < n; ++a)
+    for (int b = 0; b < n; ++b)
+      o.W[a * n + b] = (double)(B.D[a * n + b] - B.gcL[a] * B.lm[b] - B.gcR[a] * B.lp[b]);
   return o;
 }
 

@@ -25,6 +25,8 @@ struct Ops1D {
   double gcL[kMaxN];        // correction from the face at xi = -1, multiplied by its sign -1:
                             // the derivative of g_L at x_a
   double gcR[kMaxN];        // derivative of g_R at x_a (face at xi = +1)
+  double W[kMaxN * kMaxN];  // W[a*n + b] = D[a*n + b] - gcL[a] lm[b] - gcR[a] lp[b]: the divergence
+                            // with the correction's own traces folded in (see k_volume)
 };
 
 // Tables of the closure's features: Lm[a*n + i] = orthonormal Legendre a at x_i times the

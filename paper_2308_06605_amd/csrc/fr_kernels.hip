@@ -47,78 +47,64 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_PREPASS(P)) v
                                                            real *__restrict__ face, int64_t E,
                                                            OpsT<real> ops) {
   using C = Cfg<P>;
-  constexpr int N = C::N, NS = C::NS, NFP = C::NFP, NF = C::NF, EPB = EPBX;
+  constexpr int N = C::N, NS = C::NS, NFP = C::NFP, EPB = EPBX;
   constexpr int NG = VISC ? 15 : 0;
-  __shared__ real sU[EPB][5][NS];
-  __shared__ real sG[EPB][NG > 0 ? NG : 1][NS];
+  __shared__ real sAll[EPB][(5 + NG) * NS];  // the state, then its broken gradient [i][v]
   const int slot = threadIdx.x / NS, t = threadIdx.x - slot * NS;
   const int64_t e = (int64_t)blockIdx.x * EPB + slot;
   const bool act = e < E;
-  const int i0 = t % N, i1 = (t / N) % N, i2 = plane_index<N, EPB>(t);
+  const int idx[3] = {t % N, (t / N) % N, plane_index<N, EPB>(t)};
+  real *sU = sAll[slot], *sG = sU + 5 * NS;
   if (act) {
 #pragma unroll
-    for (int v = 0; v < 5; ++v) sU[slot][v][t] = real(X[(e * 5 + v) * NS + t]);
+    for (int v = 0; v < 5; ++v) sU[v * NS + t] = real(X[(e * 5 + v) * NS + t]);
   }
-  __syncthreads();
+  elem_sync<NS>();
   if (VISC && act) {
     real ja[9];
 #pragma unroll
     for (int c = 0; c < 9; ++c) ja[c] = geo[(e * 10 + c) * NS + t];
     const real iJ = geo[(e * 10 + 9) * NS + t];
-    constexpr int UNV = P >= 6 ? 1 : 5;  // bounds the loads in flight at high degree
-#pragma unroll UNV
-    for (int v = 0; v < 5; ++v) {
-      real d0 = 0, d1 = 0, d2 = 0;
+    real dU[3][5];
 #pragma unroll
-      for (int c = 0; c < N; ++c) {
-        d0 += ops.D[i0 * N + c] * sU[slot][v][c + N * (i1 + N * i2)];
-        d1 += ops.D[i1 * N + c] * sU[slot][v][i0 + N * (c + N * i2)];
-        d2 += ops.D[i2 * N + c] * sU[slot][v][i0 + N * (i1 + N * c)];
+    for (int d = 0; d < 3; ++d) {
+      const int stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+      const int b0 = t - idx[d] * stride;
+      real row[N];
+#pragma unroll
+      for (int c = 0; c < N; ++c) row[c] = ops.D[idx[d] * N + c];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        real acc = 0;
+#pragma unroll
+        for (int c = 0; c < N; ++c) acc = fma(row[c], sU[v * NS + b0 + c * stride], acc);
+        dU[d][v] = acc;
       }
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
 #pragma unroll
       for (int ii = 0; ii < 3; ++ii) {
-        real g = ja[ii] * d0;
-        g += ja[3 + ii] * d1;
-        g += ja[6 + ii] * d2;
-        sG[slot][ii * 5 + v][t] = iJ * g;
+        real g = dot3(ja[ii], dU[0][v], ja[3 + ii], dU[1][v], ja[6 + ii], dU[2][v]);
+        sG[(ii * 5 + v) * NS + t] = iJ * g;
       }
-    }
   }
-  __syncthreads();
+  elem_sync<NS>();
   if (!act) return;
   constexpr int NVAL = VISC ? 20 : 5;
+  real *dst = face + e * 6 * 20 * NFP;
   if constexpr (kWavePerFace<NFP, EPB>) {
-    // p = 7: wave-uniform tasks (value, face), the face's 64 points on the lanes
+    // p = 7: wave-uniform tasks (value, direction), the direction's 64 lines on the lanes
     const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int a = lane % N, b = lane / N;
-    for (int k = wv; k < NVAL * 6; k += NS / 64) {
-      const int val = k / 6, f = k - 6 * val;
-      const real *src = val < 5 ? &sU[slot][val][0] : &sG[slot][(val - 5) % (NG > 0 ? NG : 1)][0];
-      face_store<NFP>(face_sum_uniform<N>(f, a, b, src, ops.lm, ops.lp),
-                      &face[((e * 6 + f) * 20 + val) * NFP + lane]);
+    for (int k = wv; k < NVAL * 3; k += NS / 64) {
+      const int val = k / 3, d = k - 3 * val;
+      real lo, hi;
+      face_sums_uniform<N>(d, lane % N, lane / N, sU + val * NS, ops.lm, ops.lp, lo, hi);
+      face_store<NFP>(lo, &dst[(2 * d * 20 + val) * NFP + lane]);
+      face_store<NFP>(hi, &dst[((2 * d + 1) * 20 + val) * NFP + lane]);
     }
-    return;
-  }
-  // items are (group of GV values, face point); consecutive threads write consecutive points
-  // of one face. With more face points than threads (p <= 4) one item carries all 20 values,
-  // which amortises the index arithmetic; at higher degree groups of 5 balance the threads.
-  constexpr int GV = (NF > NS || !VISC) ? NVAL : 5;
-  constexpr int NGRP = NVAL / GV;
-  for (int q = t; q < NGRP * NF; q += NS) {
-    const int grp = q / NF, fp = q - grp * NF;
-    const int f = fp / NFP, kk = fp - f * NFP;
-    const int a = kk % N, b = kk / N, d = f >> 1;
-    const bool hi = f & 1;
-    real *dst = face + ((e * 6 + f) * 20 + GV * grp) * NFP + kk;
-#pragma unroll
-    for (int v = 0; v < GV; ++v) {
-      const int val = GV * grp + v;
-      const real *src = val < 5 ? &sU[slot][val][0] : &sG[slot][(val - 5) % (NG > 0 ? NG : 1)][0];
-      real acc = 0;
-#pragma unroll
-      for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS64(P)>(hi, ops.lm, ops.lp, c) * src[line_pt<N>(d, c, a, b)];
-      face_store<NFP>(acc, &dst[v * NFP]);
-    }
+  } else {
+    write_traces<N, NVAL, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
   }
 }
 
@@ -273,8 +259,19 @@ __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const 
 // ------------------------------------------------------------------------------------------
 // K3: volume kernel. Per element: gathers its faces' jumps and common fluxes into LDS, forms
 // the corrected gradient (g_DG correction by U^C - U), the pointwise flux F_inv - F_v, the
-// transformed divergence sum_n D_n F^n plus the flux correction
-// (s F^{I,perp} - F^d_f) g'(xi_d), R = -div/|J|, and the RK register update.
+// transformed divergence with the flux correction, R = -div/|J|, and the RK register update.
+//
+// Divergence: sum_c D[a][c] F(c) + (F^I_- - F_-) g_L'(a) + (F^I_+ - F_+) g_R'(a), with the traces
+// F_-/+ = sum_c l_c(-/+1) F(c), is sum_c W[a][c] F(c) + F^I_- g_L'(a) + F^I_+ g_R'(a) with
+// W = D - g_L' l(-1)^T - g_R' l(+1)^T. Taken that way it needs no traces: per direction one
+// exchange through LDS instead of three phases (it was 40% of one wave's time at p = 3). Its
+// round-off against long double, on fluxes of a constant plus 10^-3 variations, is 0.7 to 1.2
+// times that of the other form in FP64 and 0.6 to 1.3 times in FP32 over p = 1..7 (rms; the
+// largest error is smaller at all but p = 1 and p = 7, by up to 30%). With the closure (SGS) the
+// traces stay: its features take the logarithm of modal energies that vanish by symmetry but for
+// round-off, so that runs to t = 4.5 move by 2e-8 in E_k with any other order of these sums, and
+// the closure's stored evaluation is compared to 1e-8. Each point then takes both traces from the
+// line it has read for its derivative.
 // ------------------------------------------------------------------------------------------
 // PRE: also run the next stage's pre-pass on the state this stage stores (see the end); the
 // profiles call that instance k_volume_pre.
@@ -293,43 +290,51 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
   constexpr bool SPX = PRE && VISC && !LDG && P <= 5;
   constexpr int NJ0 = (VISC ? 10 : 5) * NF;
   constexpr int NJ = SPX && 15 * NS > NJ0 ? 15 * NS : NJ0;
-  __shared__ real sUall[EPB][5 * NS];  // state, then the transformed flux of one direction
-  __shared__ real sJall[EPB][NJ];      // [5][NF] flux along +xi_d (then its jump); [5][NF] U^C - U
+  // [5][NS] state, then the transformed flux of one direction; [5][NF] common flux along +xi_d;
+  // [5][NF] U^C - U
+  __shared__ real sAll[EPB][5 * NS + NJ];
   // At p = 7 (two blocks per CU by registers) the LDS the two blocks leave free keeps NMS of the
   // ten metric terms each thread loaded, for the fused pre-pass of the next stage, which then
   // reads only the others again from HBM (each thread reads back its own terms: no barrier).
   constexpr int NMS = PRE && VISC && !LDG && kWavePerFace<NFP, EPB> && sizeof(real) == 8 ? 7 : 0;
   __shared__ real sMet[NMS > 0 ? NMS : 1][NMS > 0 ? NS : 1];
-  // Operator entries indexed by a lane's own point (rows of D, the correction derivatives at
-  // the solution points) are read from an LDS copy. From the kernel argument each would be a
+  // Operator entries indexed by a lane's own point (rows of D and W, the correction derivatives
+  // at the solution points) are read from an LDS copy. From the kernel argument each would be a
   // vector memory load, and those complete in issue order: one issued after the RK-register
   // loads waits for HBM. Rows indexed by the wave-uniform plane index stay scalar loads. The
   // copy is left out where its bytes would cost a block per CU (p = 3, whose blocks fill the
-  // LDS exactly). (Written as conditional expressions: through accessor lambdas the code
-  // without the copy compiled differently and spilled more.)
+  // LDS exactly).
   constexpr bool UNI2 = N * N == 64 && EPB == 1;
-  constexpr int LDS0 = (int)sizeof(real) * (EPB * 5 * NS + EPB * NJ + NMS * NS);
-  constexpr bool OPL = lds_copy_fits(LDS0, (int)sizeof(real) * (N * N + 2 * N), EPB * NS);
-  __shared__ real sOp[OPL ? N * N + 2 * N : 1];
+  constexpr int NOP = kOpEntries<N>;
+  constexpr int LDS0 = (int)sizeof(real) * (EPB * (5 * NS + NJ) + NMS * NS);
+  constexpr bool OPL = lds_copy_fits(LDS0, (int)sizeof(real) * NOP, EPB * NS);
+  // Without room for that copy, the viscous kernel keeps one per element in the face jumps'
+  // entries, which nothing reads after the gradient phase; each thread loads its entry with the
+  // kernel's first loads. The tail's rows of D are read from it before the gradient takes its
+  // place.
+  constexpr bool OPX = !OPL && VISC && NOP <= 5 * NF && NOP <= NS;
+  __shared__ real sOp[OPL ? NOP : 1];
   if (OPL)
-    for (int i = threadIdx.x; i < N * N + 2 * N; i += EPB * NS)
-      sOp[i] = i < N * N ? ops.D[i] : (i < N * N + N ? ops.gcL[i - N * N] : ops.gcR[i - N * N - N]);
+    for (int i = threadIdx.x; i < NOP; i += EPB * NS) sOp[i] = op_entry<N>(ops, i);
   const int slot = threadIdx.x / NS, t = threadIdx.x - slot * NS;
   const int64_t e = (int64_t)blockIdx.x * EPB + slot;
   const bool act = e < E;
   const int idx[3] = {t % N, (t / N) % N, plane_index<N, EPB>(t)};
-  real *sU = sUall[slot];
-  real *sJ = sJall[slot];
+  real *sU = sAll[slot], *sJ = sU + 5 * NS;
+  real *sX = sJ + 5 * NF;           // the jumps
+  const real *sT = OPL ? sOp : sX;  // the operator entries' copy
+  constexpr int oL = N * N, oR = N * N + N, oW = N * N + 2 * N;
 
-  // every global load is issued here, before the first barrier: the state, the metric terms,
-  // the RK registers and this element's share of its faces' jumps and fluxes
+  // every global load is issued here, before the first barrier: the state, the metric terms
+  // and this element's share of its faces' jumps and fluxes
   constexpr int R = (NF + NS - 1) / NS;  // face points per thread
   constexpr int NC = VISC ? 10 : 5;
-  real U[5], ja[9], iJ = 0;
+  real U[5], ja[9], iJ = 0, opv = 0;
   double Xd[5], r1[5], r2[5];
   real gv[R][NC];
   const int64_t base = e * 5 * NS + t;
   if (act) {
+    if (OPX && t < NOP) opv = op_entry<N>(ops, t);
 #pragma unroll
     for (int v = 0; v < 5; ++v) Xd[v] = X[base + v * NS];
 #pragma unroll
@@ -374,42 +379,37 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
       }
     }
   }
-  __syncthreads();
+  if (OPL) __syncthreads();  // sOp is the block's
+  else elem_sync<NS>();
   real F[3][5];
   if (act) {
     if (VISC) {
       real dU[3][5];
 #pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        real d0 = 0, d1 = 0, d2 = 0;
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-          d0 += (OPL ? sOp[idx[0] * N + c] : ops.D[idx[0] * N + c]) * sU[v * NS + c + N * (idx[1] + N * idx[2])];
-          d1 += (OPL ? sOp[idx[1] * N + c] : ops.D[idx[1] * N + c]) * sU[v * NS + idx[0] + N * (c + N * idx[2])];
-          d2 += (OPL && !UNI2 ? sOp[idx[2] * N + c] : ops.D[idx[2] * N + c]) * sU[v * NS + idx[0] + N * (idx[1] + N * c)];
-        }
-        dU[0][v] = d0;
-        dU[1][v] = d1;
-        dU[2][v] = d2;
-      }
-#pragma unroll
       for (int d = 0; d < 3; ++d) {
         const int u = d == 0 ? 1 : 0, w = d == 2 ? 1 : 2;
         const int kk = idx[u] + N * idx[w];
+        const int stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+        const int b0 = t - idx[d] * stride;
         const bool cpy = OPL && !(UNI2 && d == 2);
-        const real cL = cpy ? sOp[N * N + idx[d]] : ops.gcL[idx[d]], cR = cpy ? sOp[N * N + N + idx[d]] : ops.gcR[idx[d]];
+        real row[N];
 #pragma unroll
-        for (int v = 0; v < 5; ++v)
-          dU[d][v] += sJ[(5 + v) * NF + (2 * d) * NFP + kk] * cL + sJ[(5 + v) * NF + (2 * d + 1) * NFP + kk] * cR;
+        for (int c = 0; c < N; ++c) row[c] = cpy ? sOp[idx[d] * N + c] : ops.D[idx[d] * N + c];
+        const real cL = cpy ? sOp[oL + idx[d]] : ops.gcL[idx[d]], cR = cpy ? sOp[oR + idx[d]] : ops.gcR[idx[d]];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          real acc = 0;
+#pragma unroll
+          for (int c = 0; c < N; ++c) acc = fma(row[c], sU[v * NS + b0 + c * stride], acc);
+          dU[d][v] = acc + fma(sX[v * NF + (2 * d) * NFP + kk], cL, sX[v * NF + (2 * d + 1) * NFP + kk] * cR);
+        }
       }
       real G[3][5];
 #pragma unroll
       for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
-          real g = ja[i] * dU[0][v];
-          g += ja[3 + i] * dU[1][v];
-          g += ja[6 + i] * dU[2][v];
+          real g = dot3(ja[i], dU[0][v], ja[3 + i], dU[1][v], ja[6 + i], dU[2][v]);
           G[i][v] = iJ * g;
         }
       real mu = ph.mu, kap = ph.kappa;
@@ -437,15 +437,12 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
     for (int v = 0; v < 5; ++v) {
       const real f0 = F[0][v], f1 = F[1][v], f2 = F[2][v];
 #pragma unroll
-      for (int d = 0; d < 3; ++d) F[d][v] = ja[d * 3 + 0] * f0 + ja[d * 3 + 1] * f1 + ja[d * 3 + 2] * f2;
+      for (int d = 0; d < 3; ++d) {
+        real f = dot3(ja[d * 3 + 0], f0, ja[d * 3 + 1], f1, ja[d * 3 + 2], f2);
+        F[d][v] = f;
+      }
     }
   }
-  // Without room for that copy, the viscous kernel keeps one for the divergence phase in slot
-  // 0's jump entries, which nothing reads after the gradient phase. It is stored after the
-  // phase's first barrier, each thread picking its entry out of the whole table read by scalar
-  // loads (which do not wait for the vector loads of the RK registers).
-  constexpr int NOP = N * N + 2 * N;
-  constexpr bool OPX = !OPL && VISC && 5 * NF + NOP <= NJ;
   // the RK registers are loaded here so that their latency overlaps the divergence phase
   if (act) {
     // (assigned per mode, not initialised up front: a live range from the kernel's start
@@ -464,74 +461,51 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
       for (int v = 0; v < 5; ++v) r1[v] = (st.stage == 4 || st.stage == 9) ? reg1[base + v * NS] : 0.0;
     }
   }
-  // divergence of the transformed flux and the flux correction, one direction at a time
+  // divergence of the transformed flux with the correction, one direction at a time
   real div[5] = {0, 0, 0, 0, 0};
-  real *sF = sU;
-  real *sOpx = &sJall[0][5 * NF];
+  auto diverge = [&](int d) {
+    const int u = d == 0 ? 1 : 0, w = d == 2 ? 1 : 2;
+    const int kk = idx[u] + N * idx[w];
+    const int stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+    const int b0 = t - idx[d] * stride;
+    const bool cpy = (OPL || OPX) && !(UNI2 && d == 2);
+    real row[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c)
+      row[c] = cpy ? sT[(SGS ? 0 : oW) + idx[d] * N + c] : (SGS ? ops.D[idx[d] * N + c] : ops.W[idx[d] * N + c]);
+    const real cL = cpy ? sT[oL + idx[d]] : ops.gcL[idx[d]], cR = cpy ? sT[oR + idx[d]] : ops.gcR[idx[d]];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      const real fl = sJ[v * NF + (2 * d) * NFP + kk], fr = sJ[v * NF + (2 * d + 1) * NFP + kk];
+      real acc = SGS ? real(0) : fma(fr, cR, fl * cL), lo = 0, hi = 0;
+#pragma unroll
+      for (int c = 0; c < N; ++c) {
+        const real x = sU[v * NS + b0 + c * stride];
+        acc = fma(row[c], x, acc);
+        if (SGS) {
+          lo = fma(ops.lm[c], x, lo);
+          hi = fma(ops.lp[c], x, hi);
+        }
+      }
+      div[v] += acc;
+      if (SGS) div[v] += fma(fl - lo, cL, (fr - hi) * cR);
+    }
+  };
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    __syncthreads();
+    elem_sync<NS>();
     if (act) {
 #pragma unroll
-      for (int v = 0; v < 5; ++v) sF[v * NS + t] = F[d][v];
+      for (int v = 0; v < 5; ++v) sU[v * NS + t] = F[d][v];
+      if (OPX && d == 0 && t < NOP) sX[t] = opv;
     }
-    if (OPX && d == 0 && threadIdx.x < NOP) {
-      real opv = 0;
-#pragma unroll
-      for (int i = 0; i < NOP; ++i)
-        if ((int)threadIdx.x == i) opv = i < N * N ? ops.D[i] : (i < N * N + N ? ops.gcL[i - N * N] : ops.gcR[i - N * N - N]);
-      sOpx[threadIdx.x] = opv;
-    }
-    __syncthreads();
-    if (act) {
-#pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        real acc = 0;
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-          const int id = d == 0 ? c + N * (idx[1] + N * idx[2])
-                                : (d == 1 ? idx[0] + N * (c + N * idx[2]) : idx[0] + N * (idx[1] + N * c));
-          acc += (OPL && !(UNI2 && d == 2) ? sOp[idx[d] * N + c] : (OPX ? sOpx[idx[d] * N + c] : ops.D[idx[d] * N + c])) * sF[v * NS + id];
-        }
-        div[v] += acc;
-      }
-      // the transformed flux at the two faces normal to d: at p = 7 wave-uniform tasks (value,
-      // face) over all threads, otherwise a thread per face point
-      if constexpr (kWavePerFace<NFP, EPB>) {
-        const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
-        for (int k = wv; k < 10; k += NS / 64) {
-          const int v = k >> 1, f = 2 * d + (k & 1);
-          sJ[v * NF + f * NFP + lane] -= face_sum_uniform<N>(f, lane % N, lane / N, &sF[v * NS], ops.lm, ops.lp);
-        }
-      } else {
-        for (int fp = t; fp < 2 * NFP; fp += NS) {
-          const int f = 2 * d + fp / NFP, kk = fp % NFP;
-          const int a = kk % N, b = kk / N;
-          const bool hi = f & 1;
-#pragma unroll
-          for (int v = 0; v < 5; ++v) {
-            real acc = 0;
-#pragma unroll
-            for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS64(P)>(hi, ops.lm, ops.lp, c) * sF[v * NS + line_pt<N>(d, c, a, b)];
-            sJ[v * NF + f * NFP + kk] -= acc;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    if (act) {
-      const int u = d == 0 ? 1 : 0, w = d == 2 ? 1 : 2;
-      const int kk = idx[u] + N * idx[w];
-      const bool cpy = OPL && !(UNI2 && d == 2);
-      const real cL = cpy ? sOp[N * N + idx[d]] : (OPX ? sOpx[N * N + idx[d]] : ops.gcL[idx[d]]);
-      const real cR = cpy ? sOp[N * N + N + idx[d]] : (OPX ? sOpx[N * N + N + idx[d]] : ops.gcR[idx[d]]);
-#pragma unroll
-      for (int v = 0; v < 5; ++v) div[v] += sJ[v * NF + (2 * d) * NFP + kk] * cL + sJ[v * NF + (2 * d + 1) * NFP + kk] * cR;
-    }
+    elem_sync<NS>();
+    if (act) diverge(d);
   }
+  if (PRE) elem_sync<NS>();
   // R = -div / |J| plus the source, and the RK register update, one variable at a time. With
-  // PRE the stored state also goes to sU at once (nothing reads sU after the last direction's
-  // divergence), so it is not held in registers across the barrier below.
+  // PRE the stored state also goes to sU at once (nothing reads sU any more), so it is not held
+  // in registers across the barrier below.
   if (act) {
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
@@ -546,202 +520,104 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
   // arithmetic as k_prepass. This saves that kernel's reads of the state; the metric terms are
   // loaded again here (through a pointer without __restrict__, so the loads stay after the
   // stores above and are not kept live across the divergence phase). The LDS of the divergence
-  // phase is reused: the values in sU, the gradient in sJ in chunks of VPC variables
-  // (3 VPC N_s <= 10 N_f).
+  // phase is reused: the values in sU, the gradient in sJ, whole (SPX) or in chunks of VPC
+  // variables (3 VPC N_s <= 10 N_f).
   constexpr bool GRAD = VISC && !LDG;
   constexpr int VPC = SPX || (20 / N) >= 5 ? 5 : 20 / N;
-  constexpr int UNW = P >= 6 ? 1 : VPC;  // bounds the LDS loads in flight at high degree
-  __syncthreads();
-  // face point fp of this element: the line through it along its face's normal direction runs
-  // over sU[b0 + c * stride], c = 0..N-1 (the index line_pt gives, without per-lane branches)
-  auto line = [&](int fp, int &f, int &kk, int &b0, int &stride) {
-    f = fp / NFP;
-    kk = fp - f * NFP;
-    const int a = kk % N, b = kk / N, d = f >> 1;
-    stride = d == 0 ? 1 : (d == 1 ? N : N * N);
-    b0 = d == 0 ? N * kk : (d == 1 ? a + N * N * b : kk);
-  };
-  // With a single gradient chunk (p <= 3) the gradient is formed first and the values and the
-  // gradient go to the faces in one pass, in items of five independent sums (as k_prepass);
-  // otherwise the values first, then the gradient chunk by chunk.
+  constexpr bool DROW = OPX && GRAD;  // this thread's rows of D from the copy in sX
+  real Dr[DROW ? 3 : 1][DROW ? N : 1];
+  if (DROW && act) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int c = 0; c < N; ++c) Dr[DROW ? d : 0][DROW ? c : 0] = sT[idx[d] * N + c];
+  }
+  elem_sync<NS>();
+  real *dst = face + e * 6 * 20 * NFP;
   real jb[9], iJb = 0;
   auto load_metric = [&]() {
 #pragma unroll
     for (int c = 0; c < 9; ++c) jb[c] = c < NMS ? sMet[c][t] : geo_again[(e * 10 + c) * NS + t];
     iJb = 9 < NMS ? sMet[9 < NMS ? 9 : 0][t] : geo_again[(e * 10 + 9) * NS + t];
   };
-  // gradient components of the five variables to sJ[(v * 3 + ii) * NS + t] (single chunk)
-  auto gradient = [&]() {
-#pragma unroll UNW
-    for (int v = 0; v < 5; ++v) {
-      real d0 = 0, d1 = 0, d2 = 0;
+  // broken gradient of the nv variables from v0 on to sJ[(ii * nv + w) * NS + t]
+  auto gradient = [&](int v0, int nv) {
+    real dU[3][VPC];
 #pragma unroll
-      for (int c = 0; c < N; ++c) {
-        d0 += (OPL ? sOp[idx[0] * N + c] : ops.D[idx[0] * N + c]) * sU[v * NS + c + N * (idx[1] + N * idx[2])];
-        d1 += (OPL ? sOp[idx[1] * N + c] : ops.D[idx[1] * N + c]) * sU[v * NS + idx[0] + N * (c + N * idx[2])];
-        d2 += (OPL && !UNI2 ? sOp[idx[2] * N + c] : ops.D[idx[2] * N + c]) * sU[v * NS + idx[0] + N * (idx[1] + N * c)];
+    for (int d = 0; d < 3; ++d) {
+      const int stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+      const int b0 = t - idx[d] * stride;
+      real row[N];
+#pragma unroll
+      for (int c = 0; c < N; ++c)
+        row[c] = DROW ? Dr[DROW ? d : 0][DROW ? c : 0] : (OPL && !(UNI2 && d == 2) ? sOp[idx[d] * N + c] : ops.D[idx[d] * N + c]);
+#pragma unroll
+      for (int w = 0; w < VPC; ++w) {
+        real acc = 0;
+        if (w < nv) {
+#pragma unroll
+          for (int c = 0; c < N; ++c) acc = fma(row[c], sU[(v0 + w) * NS + b0 + c * stride], acc);
+        }
+        dU[d][w] = acc;
       }
+    }
 #pragma unroll
-      for (int ii = 0; ii < 3; ++ii) {
-        real g = jb[ii] * d0;
-        g += jb[3 + ii] * d1;
-        g += jb[6 + ii] * d2;
-        sJ[(v * 3 + ii) * NS + t] = iJb * g;
+    for (int w = 0; w < VPC; ++w) {
+      if (w < nv) {
+#pragma unroll
+        for (int ii = 0; ii < 3; ++ii) {
+          real g = dot3(jb[ii], dU[0][w], jb[3 + ii], dU[1][w], jb[6 + ii], dU[2][w]);
+          sJ[(ii * nv + w) * NS + t] = iJb * g;
+        }
       }
     }
   };
-  if constexpr (kWavePerFace<NFP, EPB>) {
-    // p = 7: wave-uniform tasks (value or gradient component, face), 64 face points per task
-    const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int a = lane % N, b = lane / N;
-    if (act) {
-      for (int k = wv; k < 5 * 6; k += NS / 64) {
-        const int v = k / 6, f = k - 6 * v;
-        face_store<NFP>(face_sum_uniform<N>(f, a, b, &sU[v * NS], ops.lm, ops.lp),
-                        &face[((e * 6 + f) * 20 + v) * NFP + lane]);
-      }
-    }
-    if (GRAD) {
-      if (act) load_metric();
-#pragma unroll
-      for (int v0 = 0; v0 < 5; v0 += VPC) {
-        const int nv = 5 - v0 < VPC ? 5 - v0 : VPC;
-        if (act) {
-#pragma unroll UNW
-          for (int w = 0; w < VPC; ++w) {
-            if (w < nv) {
-              const int v = v0 + w;
-              real d0 = 0, d1 = 0, d2 = 0;
-#pragma unroll
-              for (int c = 0; c < N; ++c) {
-                d0 += (OPL ? sOp[idx[0] * N + c] : ops.D[idx[0] * N + c]) * sU[v * NS + c + N * (idx[1] + N * idx[2])];
-                d1 += (OPL ? sOp[idx[1] * N + c] : ops.D[idx[1] * N + c]) * sU[v * NS + idx[0] + N * (c + N * idx[2])];
-                d2 += (OPL && !UNI2 ? sOp[idx[2] * N + c] : ops.D[idx[2] * N + c]) * sU[v * NS + idx[0] + N * (idx[1] + N * c)];
-              }
-#pragma unroll
-              for (int ii = 0; ii < 3; ++ii) {
-                real g = jb[ii] * d0;
-                g += jb[3 + ii] * d1;
-                g += jb[6 + ii] * d2;
-                sJ[(w * 3 + ii) * NS + t] = iJb * g;
-              }
-            }
-          }
-        }
-        __syncthreads();
-        if (act) {
-          for (int k = wv; k < 3 * nv * 6; k += NS / 64) {
-            const int ci = k / 6, f = k - 6 * ci;
-            const int v = v0 + ci / 3, ii = ci - (ci / 3) * 3;
-            face_store<NFP>(face_sum_uniform<N>(f, a, b, &sJ[ci * NS], ops.lm, ops.lp),
-                            &face[((e * 6 + f) * 20 + 5 + ii * 5 + v) * NFP + lane]);
-          }
-        }
-        __syncthreads();
-      }
-    }
-    return;
-  }
-  if (GRAD && VPC == 5) {
+  if constexpr (GRAD && VPC == 5) {
+    // one pass: the gradient beside the values, then the traces of all twenty
     if (act) {
       load_metric();
-      gradient();
+      gradient(0, 5);
     }
-    __syncthreads();
-    // items (groups, face point) of GG of the four groups (group 0 the values, group 1 + ii the
-    // d/dx_ii of the five variables: slot 5 + ii * 5 + v; variable v's sits at
-    // sJ[(v * 3 + ii) * NS]); each item works out its line and interpolation weights once
-    constexpr int GG = FR_TAIL_GROUPS64(P);
-    static_assert(GG == 1 || GG == 2 || GG == 4, "groups per item divide the four groups");
-    if (act) {
-      for (int q = t; q < (4 / GG) * NF; q += NS) {
-        const int gi = q / NF;
-        int f, kk, b0, stride;
-        line(q - gi * NF, f, kk, b0, stride);
-        const bool hi = f & 1;
-        real cf[N];
-#pragma unroll
-        for (int c = 0; c < N; ++c) cf[c] = pick_end<FR_SCALAR_ENDS64(P)>(hi, ops.lm, ops.lp, c);
-#pragma unroll
-        for (int gg = 0; gg < GG; ++gg) {
-          const int grp = gi * GG + gg;
-          real *dst = face + ((e * 6 + f) * 20 + 5 * grp) * NFP + kk;
-#pragma unroll
-          for (int v = 0; v < 5; ++v) {
-            const real *src = grp == 0 ? &sU[v * NS] : &sJ[(v * 3 + grp - 1) * NS];
-            real acc = 0;
-#pragma unroll
-            for (int c = 0; c < N; ++c) acc += cf[c] * src[b0 + c * stride];
-            face_store<NFP>(acc, &dst[v * NFP]);
-          }
-        }
-      }
-    }
+    elem_sync<NS>();
+    if (act) write_traces<N, 20, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
     return;
   }
-  // several chunks (p >= 4, where N_f <= N_s): items are (value, face point), which keeps
-  // more of the threads busy than one item per face point
-  if (act) {
-    for (int q = t; q < 5 * NF; q += NS) {
-      const int v = q / NF;
-      int f, kk, b0, stride;
-      line(q - v * NF, f, kk, b0, stride);
-      const bool hi = f & 1;
-      real acc = 0;
-#pragma unroll
-      for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS64(P)>(hi, ops.lm, ops.lp, c) * sU[v * NS + b0 + c * stride];
-      face_store<NFP>(acc, &face[((e * 6 + f) * 20 + v) * NFP + kk]);
+  // several chunks (p >= 6): the traces of the values, then of the gradient chunk by chunk
+  const int lane = t & 63, wv = kWavePerFace<NFP, EPB> ? __builtin_amdgcn_readfirstlane(t >> 6) : 0;
+  auto tasks = [&](const real *src, int n, auto slot_of) {
+    // p = 7: wave-uniform tasks (array, direction), the direction's 64 lines on the lanes
+    for (int k = wv; k < n * 3; k += NS / 64) {
+      const int ci = k / 3, d = k - 3 * ci;
+      real lo, hi;
+      face_sums_uniform<N>(d, lane % N, lane / N, src + ci * NS, ops.lm, ops.lp, lo, hi);
+      face_store<NFP>(lo, &dst[(2 * d * 20 + slot_of(ci)) * NFP + lane]);
+      face_store<NFP>(hi, &dst[((2 * d + 1) * 20 + slot_of(ci)) * NFP + lane]);
     }
+  };
+  if (act) {
+    if constexpr (kWavePerFace<NFP, EPB>) tasks(sU, 5, [](int v) { return v; });
+    else write_traces<N, 5, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
   }
-  if (GRAD) {
+  if constexpr (GRAD) {
     // (the metric terms are loaded after the values pass, so they are not live across it)
     if (act) load_metric();
+    constexpr int NCH = (5 + VPC - 1) / VPC;
 #pragma unroll
-    for (int v0 = 0; v0 < 5; v0 += VPC) {
-      const int nv = 5 - v0 < VPC ? 5 - v0 : VPC;
-      // (written out rather than through gradient(): the compiler then spills 28 instead of
-      // 52 bytes per lane at p = 7)
+    for (int k = 0; k < NCH; ++k) {
+      const int v0 = k * VPC, nv = 5 - v0 < VPC ? 5 - v0 : VPC;
+      if (act) gradient(v0, nv);
+      elem_sync<NS>();
       if (act) {
-#pragma unroll UNW
-        for (int w = 0; w < VPC; ++w) {
-          if (w < nv) {
-            const int v = v0 + w;
-            real d0 = 0, d1 = 0, d2 = 0;
-#pragma unroll
-            for (int c = 0; c < N; ++c) {
-              d0 += (OPL ? sOp[idx[0] * N + c] : ops.D[idx[0] * N + c]) * sU[v * NS + c + N * (idx[1] + N * idx[2])];
-              d1 += (OPL ? sOp[idx[1] * N + c] : ops.D[idx[1] * N + c]) * sU[v * NS + idx[0] + N * (c + N * idx[2])];
-              d2 += (OPL && !UNI2 ? sOp[idx[2] * N + c] : ops.D[idx[2] * N + c]) * sU[v * NS + idx[0] + N * (idx[1] + N * c)];
-            }
-#pragma unroll
-            for (int ii = 0; ii < 3; ++ii) {
-              real g = jb[ii] * d0;
-              g += jb[3 + ii] * d1;
-              g += jb[6 + ii] * d2;
-              sJ[(w * 3 + ii) * NS + t] = iJb * g;
-            }
-          }
-        }
+        // component ci = ii * nv + w of the chunk is d/dx_ii of variable v0 + w
+        auto slot_of = [&](int ci) { return 5 + (ci / nv) * 5 + v0 + ci % nv; };
+        if constexpr (kWavePerFace<NFP, EPB>) tasks(sJ, 3 * nv, slot_of);
+        else if (nv == VPC) write_traces<N, 3 * VPC, 1>(t, sJ, ops.lm, ops.lp, dst, 20, slot_of);
+        else write_traces<N, 3 * (5 - VPC * (NCH - 1)), 1>(t, sJ, ops.lm, ops.lp, dst, 20, slot_of);
       }
-      __syncthreads();
-      if (act) {
-        for (int q = t; q < 3 * nv * NF; q += NS) {
-          const int ci = q / NF;
-          const int v = v0 + ci / 3, ii = ci - (ci / 3) * 3;
-          int f, kk, b0, stride;
-          line(q - ci * NF, f, kk, b0, stride);
-          const bool hi = f & 1;
-          real acc = 0;
-#pragma unroll
-          for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS64(P)>(hi, ops.lm, ops.lp, c) * sJ[ci * NS + b0 + c * stride];
-          face_store<NFP>(acc, &face[((e * 6 + f) * 20 + 5 + ii * 5 + v) * NFP + kk]);
-        }
-      }
-      __syncthreads();
+      elem_sync<NS>();
     }
   }
 }
-
 
 // ------------------------------------------------------------------------------------------
 // LDG: each element's corrected gradient (section "FR Algorithm", the viscous flux by the local
@@ -1086,7 +962,10 @@ static int launch_stage_t(DeviceMesh &dm, const double *X, StageArgs st, double 
                           double *ms) {
   using C = Cfg<P>;
   OpsT<real> ops;
-  for (int i = 0; i < kMaxN * kMaxN; ++i) ops.D[i] = real(dm.ops.D[i]);
+  for (int i = 0; i < kMaxN * kMaxN; ++i) {
+    ops.D[i] = real(dm.ops.D[i]);
+    ops.W[i] = real(dm.ops.W[i]);
+  }
   for (int i = 0; i < kMaxN; ++i) {
     ops.lm[i] = real(dm.ops.lm[i]);
     ops.lp[i] = real(dm.ops.lp[i]);

@@ -136,9 +136,8 @@ __device__ __forceinline__ void prepass32_body(unsigned blk, const double *__res
   constexpr int N = C::N, NS = C::NS, NFP = C::NFP, NF = C::NF, EPB = EPBX;
   constexpr int NG = VISC ? 15 : 1;
   // (16-byte aligned: the p = 7 face sums read whole lines with 16-byte loads)
-  __shared__ alignas(16) float sU[EPB][5][NS];
-  __shared__ alignas(16) double sM[EPB][3][NS];
-  __shared__ alignas(16) float sG[EPB][NG][NS];
+  __shared__ alignas(16) float sAll[EPB][(5 + NG) * NS];  // U', then its broken gradient [i][v]
+  __shared__ alignas(16) double sMall[EPB][3 * NS];
   constexpr bool WPF = kWavePerFace<NFP, EPB>;
   __shared__ float sRot[WPF ? 4 * N : 1];  // the rotated face sums' weights, FP32 and FP64
   __shared__ double sRotd[WPF ? 4 * N : 1];
@@ -150,95 +149,78 @@ __device__ __forceinline__ void prepass32_body(unsigned blk, const double *__res
   const int slot = threadIdx.x / NS, t = threadIdx.x - slot * NS;
   const int64_t e = (int64_t)blk * EPB + slot;
   const bool act = e < E;
-  const int i0 = t % N, i1 = (t / N) % N, i2 = plane_index<N, EPB>(t);
+  const int idx[3] = {t % N, (t / N) % N, plane_index<N, EPB>(t)};
+  float *sU = sAll[slot], *sG = sU + 5 * NS;
+  double *sM = sMall[slot];
   if (act) {
     const double x0 = X[(e * 5 + 0) * NS + t], x4 = X[(e * 5 + 4) * NS + t];
-    sU[slot][0][t] = float(x0 - ref.rho_d);
-    sU[slot][4][t] = float(x4 - ref.E_d);
+    sU[t] = float(x0 - ref.rho_d);
+    sU[4 * NS + t] = float(x4 - ref.E_d);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
       const double m = X[(e * 5 + 1 + i) * NS + t];
-      sU[slot][1 + i][t] = float(m);
-      sM[slot][i][t] = m;
+      sU[(1 + i) * NS + t] = float(m);
+      sM[i * NS + t] = m;
     }
   }
-  __syncthreads();
+  elem_sync<NS>();
   if (VISC && act) {
     float ja[9];
 #pragma unroll
     for (int c = 0; c < 9; ++c) ja[c] = geo32[(e * 10 + c) * NS + t];
     const float iJ = geo32[(e * 10 + 9) * NS + t];
+    float dU[3][5];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      float d0 = 0, d1 = 0, d2 = 0;
+    for (int d = 0; d < 3; ++d) {
+      const int stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+      const int b0 = t - idx[d] * stride;
+      float row[N];
 #pragma unroll
-      for (int c = 0; c < N; ++c) {
-        d0 += ops.D[i0 * N + c] * sU[slot][v][c + N * (i1 + N * i2)];
-        d1 += ops.D[i1 * N + c] * sU[slot][v][i0 + N * (c + N * i2)];
-        d2 += ops.D[i2 * N + c] * sU[slot][v][i0 + N * (i1 + N * c)];
-      }
+      for (int c = 0; c < N; ++c) row[c] = ops.D[idx[d] * N + c];
 #pragma unroll
-      for (int ii = 0; ii < 3; ++ii) sG[slot][(ii * 5 + v) % NG][t] = iJ * (ja[ii] * d0 + ja[3 + ii] * d1 + ja[6 + ii] * d2);
-    }
-  }
-  __syncthreads();
-  if (!act) return;
-  if constexpr (kWavePerFace<NFP, EPB>) {
-    // p = 7: wave-uniform tasks (value, face), the face's 64 points on the lanes: U' (5), the
-    // gradient (15), then the FP64 momentum (3)
-    const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int a = lane % N, b = lane / N;
-    constexpr int NV = VISC ? 20 : 5;
-    for (int k = wv; k < (NV + 3) * 6; k += NS / 64) {
-      const int val = k / 6, f = k - 6 * val;
-      if (val < NV) {
-        const float *src = val < 5 ? &sU[slot][val][0] : &sG[slot][(val - 5) % NG][0];
-        face_store<NFP>(face_sum_uniform<N, true>(f, a, b, src, ops.lm, ops.lp, sRot),
-                        &face32[((e * 6 + f) * 20 + val) * NFP + lane]);
-      } else {
-        const int i = val - NV;
-        face_store<NFP>(face_sum_uniform<N, true>(f, a, b, &sM[slot][i][0], opsd.lm, opsd.lp, sRotd),
-                        &facem[((e * 6 + f) * 3 + i) * NFP + lane]);
-      }
-    }
-    return;
-  }
-  for (int fp = t; fp < NF; fp += NS) {
-    const int f = fp / NFP, kk = fp - f * NFP;
-    const int a = kk % N, b = kk / N, d = f >> 1;
-    const bool hi = f & 1;
-    float ell[N];
-    double elld[N];
-#pragma unroll
-    for (int c = 0; c < N; ++c) {
-      ell[c] = pick_end<FR_SCALAR_ENDS32(P)>(hi, ops.lm, ops.lp, c);
-      elld[c] = pick_end<FR_SCALAR_ENDS32(P)>(hi, opsd.lm, opsd.lp, c);
-    }
-    float *dst = face32 + ((e * 6 + f) * 20) * NFP + kk;
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      float acc = 0;
-#pragma unroll
-      for (int c = 0; c < N; ++c) acc += ell[c] * sU[slot][v][line_pt<N>(d, c, a, b)];
-      face_store<NFP>(acc, &dst[v * NFP]);
-    }
-    if (VISC) {
-#pragma unroll 5
-      for (int g = 0; g < 15; ++g) {
+      for (int v = 0; v < 5; ++v) {
         float acc = 0;
 #pragma unroll
-        for (int c = 0; c < N; ++c) acc += ell[c] * sG[slot][g % NG][line_pt<N>(d, c, a, b)];
-        face_store<NFP>(acc, &dst[(5 + g) * NFP]);
+        for (int c = 0; c < N; ++c) acc = fma(row[c], sU[v * NS + b0 + c * stride], acc);
+        dU[d][v] = acc;
       }
     }
-    double *dm = facem + ((e * 6 + f) * 3) * NFP + kk;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      double acc = 0;
+    for (int v = 0; v < 5; ++v)
 #pragma unroll
-      for (int c = 0; c < N; ++c) acc += elld[c] * sM[slot][i][line_pt<N>(d, c, a, b)];
-      face_store<NFP>(acc, &dm[i * NFP]);
+      for (int ii = 0; ii < 3; ++ii) {
+        float g = dot3(ja[ii], dU[0][v], ja[3 + ii], dU[1][v], ja[6 + ii], dU[2][v]);
+        sG[((ii * 5 + v) % NG) * NS + t] = iJ * g;
+      }
+  }
+  elem_sync<NS>();
+  if (!act) return;
+  constexpr int NV = VISC ? 20 : 5;
+  float *dst = face32 + e * 6 * 20 * NFP;
+  double *dm = facem + e * 6 * 3 * NFP;
+  if constexpr (WPF) {
+    // p = 7: wave-uniform tasks (value, direction), the direction's 64 lines on the lanes: U' (5),
+    // the gradient (15), then the FP64 momentum (3)
+    const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int a = lane % N, b = lane / N;
+    for (int k = wv; k < (NV + 3) * 3; k += NS / 64) {
+      const int val = k / 3, d = k - 3 * val;
+      if (val < NV) {
+        float lo, hi;
+        face_sums_uniform<N, true>(d, a, b, sU + val * NS, ops.lm, ops.lp, lo, hi, sRot);
+        face_store<NFP>(lo, &dst[(2 * d * 20 + val) * NFP + lane]);
+        face_store<NFP>(hi, &dst[((2 * d + 1) * 20 + val) * NFP + lane]);
+      } else {
+        const int i = val - NV;
+        double lo, hi;
+        face_sums_uniform<N, true>(d, a, b, sM + i * NS, opsd.lm, opsd.lp, lo, hi, sRotd);
+        face_store<NFP>(lo, &dm[(2 * d * 3 + i) * NFP + lane]);
+        face_store<NFP>(hi, &dm[((2 * d + 1) * 3 + i) * NFP + lane]);
+      }
     }
+  } else {
+    write_traces<N, NV, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
+    write_traces<N, 3, 1>(t, sM, opsd.lm, opsd.lp, dm, 3, [](int v) { return v; });
   }
 }
 
@@ -409,32 +391,34 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
   constexpr int NJ = SP && VISC && 15 * NS > NJ0 ? 15 * NS : NJ0;
   constexpr int NMS = SP ? 3 * NS : NS;
   // (16-byte aligned: the p = 7 face sums read whole lines with 16-byte loads)
-  __shared__ alignas(16) float sUall[EPB][5 * NS];  // U', later 4 components of the transformed flux
-  __shared__ alignas(16) double sMall[EPB][NMS];    // transformed mass flux of one direction
-  __shared__ alignas(16) float sJall[EPB][NJ];
-  __shared__ double sJmall[EPB][NF];       // mass flux along +xi_d, then its jump
+  __shared__ alignas(16) float sAll[EPB][5 * NS + NJ];  // U', later 4 components of the transformed flux; then
+                                                        // the common fluxes and jumps
+  __shared__ alignas(16) double sMall[EPB][NMS];        // transformed mass flux of one direction
+  __shared__ double sJmall[EPB][NF];                    // common mass flux along +xi_d
   // With the fused pre-pass at p = 3 and p = 7 the LDS left free at these kernels' occupancy
   // (four blocks of four waves, two of eight) keeps the FP32 metric terms each thread converts
   // from the FP64 ones it loaded (the same roundings as the FP32 geometry copy), so the tail does
   // not read that copy from HBM again; each thread reads back its own terms (no barrier).
   constexpr bool MST = PRE && VISC && (P == 3 || P == 7);
   __shared__ float sMetall[EPB][MST ? 10 * NS : 1];
-  // Operator entries indexed by a lane's own point (rows of D, the correction derivatives at
-  // the solution points) come from LDS copies, as in the FP64 volume kernel: from the kernel
+  // Operator entries indexed by a lane's own point (rows of D and W, the correction derivatives
+  // at the solution points) come from LDS copies, as in the FP64 volume kernel: from the kernel
   // argument each would be a vector memory load, which completes in issue order, after the
   // RK-register loads. Rows indexed by the wave-uniform plane index stay scalar loads; the copies
   // are left out where their bytes would cost a block per CU. (Conditional expressions rather
   // than accessor lambdas, which changed the code generated without the copies.)
   constexpr bool UNI2 = N * N == 64 && EPB == 1;
-  constexpr int NOP = N * N + 2 * N;
+  constexpr int NOF = N * N + 2 * N;  // FP32: D, gcL, gcR
+  constexpr int NOD = N * N + 2 * N;  // the mass equation: gcL, gcR, W
   constexpr int LDS0 = EPB * (4 * 5 * NS + 8 * NMS + 4 * NJ + 8 * NF + (MST ? 4 * 10 * NS : 0));
-  constexpr bool OPL = lds_copy_fits(LDS0, 12 * NOP, EPB * NS);
-  __shared__ float sOpf[OPL ? NOP : 1];
-  __shared__ double sOpd[OPL ? NOP : 1];
+  constexpr bool OPL = lds_copy_fits(LDS0, 4 * NOF + 8 * NOD, EPB * NS);
+  __shared__ float sOpf[OPL ? NOF : 1];
+  __shared__ double sOpd[OPL ? NOD : 1];
+  constexpr int oL = N * N, oR = N * N + N;
   if (OPL)
-    for (int i = threadIdx.x; i < NOP; i += EPB * NS) {
-      sOpf[i] = i < N * N ? ops.D[i] : (i < N * N + N ? ops.gcL[i - N * N] : ops.gcR[i - N * N - N]);
-      sOpd[i] = i < N * N ? opsd.D[i] : (i < N * N + N ? opsd.gcL[i - N * N] : opsd.gcR[i - N * N - N]);
+    for (int i = threadIdx.x; i < NOF; i += EPB * NS) {
+      sOpf[i] = op_entry<N>(ops, i);
+      sOpd[i] = op_entry<N>(opsd, i + N * N);
     }
   constexpr bool WPF = kWavePerFace<NFP, EPB>;
   __shared__ float sRot[WPF ? 4 * N : 1];  // the rotated face sums' weights, FP32 and FP64
@@ -448,9 +432,8 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
   const int64_t e = (int64_t)blk * EPB + slot;
   const bool act = e < E;
   const int idx[3] = {t % N, (t / N) % N, plane_index<N, EPB>(t)};
-  float *sU = sUall[slot];
+  float *sU = sAll[slot], *sJ = sU + 5 * NS;
   double *sM = sMall[slot];
-  float *sJ = sJall[slot];
   double *sJm = sJmall[slot];
   const int64_t base = e * 5 * NS + t;
   double Xd[5], jad[9], iJd = 0, r1[5], r2[5];
@@ -494,7 +477,8 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
     sU[3 * NS + t] = float(Xd[3]);
     sU[4 * NS + t] = float(Xd[4] - ref.E_d);
   }
-  __syncthreads();
+  if (OPL || WPF) __syncthreads();  // the tables are the block's
+  else elem_sync<NS>();
   float F[3][5];  // [direction][component]: 0 unused, 1-3 momentum, 4 reduced energy
   double Fm[3];   // transformed mass flux per direction (FP64)
   if (act) {
@@ -508,33 +492,32 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
       const float iJ = float(iJd);
       float dU[3][5];
 #pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        float d0 = 0, d1 = 0, d2 = 0;
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-          d0 += (OPL ? sOpf[idx[0] * N + c] : ops.D[idx[0] * N + c]) * sU[v * NS + c + N * (idx[1] + N * idx[2])];
-          d1 += (OPL ? sOpf[idx[1] * N + c] : ops.D[idx[1] * N + c]) * sU[v * NS + idx[0] + N * (c + N * idx[2])];
-          d2 += (OPL && !UNI2 ? sOpf[idx[2] * N + c] : ops.D[idx[2] * N + c]) * sU[v * NS + idx[0] + N * (idx[1] + N * c)];
-        }
-        dU[0][v] = d0;
-        dU[1][v] = d1;
-        dU[2][v] = d2;
-      }
-#pragma unroll
       for (int d = 0; d < 3; ++d) {
         const int u = d == 0 ? 1 : 0, w = d == 2 ? 1 : 2;
         const int kk = idx[u] + N * idx[w];
+        const int stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+        const int b0 = t - idx[d] * stride;
         const bool cpy = OPL && !(UNI2 && d == 2);
-        const float cL = cpy ? sOpf[N * N + idx[d]] : ops.gcL[idx[d]], cR = cpy ? sOpf[N * N + N + idx[d]] : ops.gcR[idx[d]];
+        float row[N];
 #pragma unroll
-        for (int v = 0; v < 5; ++v)
-          dU[d][v] += sJ[(4 + v) * NF + (2 * d) * NFP + kk] * cL + sJ[(4 + v) * NF + (2 * d + 1) * NFP + kk] * cR;
+        for (int c = 0; c < N; ++c) row[c] = cpy ? sOpf[idx[d] * N + c] : ops.D[idx[d] * N + c];
+        const float cL = cpy ? sOpf[oL + idx[d]] : ops.gcL[idx[d]], cR = cpy ? sOpf[oR + idx[d]] : ops.gcR[idx[d]];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          float acc = 0;
+#pragma unroll
+          for (int c = 0; c < N; ++c) acc = fma(row[c], sU[v * NS + b0 + c * stride], acc);
+          dU[d][v] = acc + fma(sJ[(4 + v) * NF + (2 * d) * NFP + kk], cL, sJ[(4 + v) * NF + (2 * d + 1) * NFP + kk] * cR);
+        }
       }
       float G[3][5];
 #pragma unroll
       for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int v = 0; v < 5; ++v) G[i][v] = iJ * (ja[i] * dU[0][v] + ja[3 + i] * dU[1][v] + ja[6 + i] * dU[2][v]);
+        for (int v = 0; v < 5; ++v) {
+          float g = dot3(ja[i], dU[0][v], ja[3 + i], dU[1][v], ja[6 + i], dU[2][v]);
+          G[i][v] = iJ * g;
+        }
       float Uf[5];
       full_state(Up, ref, Uf);
       visc_flux(Uf, G, ph, F);
@@ -553,11 +536,15 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
     for (int v = 1; v < 5; ++v) {
       const float f0 = F[0][v], f1 = F[1][v], f2 = F[2][v];
 #pragma unroll
-      for (int d = 0; d < 3; ++d)
-        F[d][v] = float(jad[d * 3 + 0]) * f0 + float(jad[d * 3 + 1]) * f1 + float(jad[d * 3 + 2]) * f2;
+      for (int d = 0; d < 3; ++d) {
+        float f = dot3(float(jad[d * 3 + 0]), f0, float(jad[d * 3 + 1]), f1, float(jad[d * 3 + 2]), f2);
+        F[d][v] = f;
+      }
     }
 #pragma unroll
-    for (int d = 0; d < 3; ++d) Fm[d] = jad[d * 3 + 0] * Xd[1] + jad[d * 3 + 1] * Xd[2] + jad[d * 3 + 2] * Xd[3];
+    for (int d = 0; d < 3; ++d) {
+      Fm[d] = dot3(jad[d * 3 + 0], Xd[1], jad[d * 3 + 1], Xd[2], jad[d * 3 + 2], Xd[3]);
+    }
     // (assigned per mode, not initialised up front: a live range from the kernel's start
     // costs the gradient phase its registers)
     if (st.mode == kModeLSRK) {
@@ -574,81 +561,57 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
       for (int v = 0; v < 5; ++v) r1[v] = (st.stage == 4 || st.stage == 9) ? reg1[base + v * NS] : 0.0;
     }
   }
+  // divergence and flux correction, one direction at a time. The mass equation takes the
+  // correction folded into W (see k_volume). The FP32 components keep the traces of the flux apart,
+  // each point taking both from the line it has read for its derivative: folded in, they rounded
+  // up to 1.7 times further from float64 (eight steps of walled channels at p = 2..5).
   float div[5] = {0, 0, 0, 0, 0};
   double divm = 0;
-  float *sF = sU;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    __syncthreads();
+    elem_sync<NS>();
     if (act) {
 #pragma unroll
-      for (int v = 1; v < 5; ++v) sF[(v - 1) * NS + t] = F[d][v];
+      for (int v = 1; v < 5; ++v) sU[(v - 1) * NS + t] = F[d][v];
       sM[t] = Fm[d];
     }
-    __syncthreads();
-    if (act) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        float acc = 0;
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-          const int id = d == 0 ? c + N * (idx[1] + N * idx[2])
-                                : (d == 1 ? idx[0] + N * (c + N * idx[2]) : idx[0] + N * (idx[1] + N * c));
-          acc += (OPL && !(UNI2 && d == 2) ? sOpf[idx[d] * N + c] : ops.D[idx[d] * N + c]) * sF[v * NS + id];
-        }
-        div[1 + v] += acc;
-      }
-      {
-        double acc = 0;
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-          const int id = d == 0 ? c + N * (idx[1] + N * idx[2])
-                                : (d == 1 ? idx[0] + N * (c + N * idx[2]) : idx[0] + N * (idx[1] + N * c));
-          acc += (OPL && !(UNI2 && d == 2) ? sOpd[idx[d] * N + c] : opsd.D[idx[d] * N + c]) * sM[id];
-        }
-        divm += acc;
-      }
-      if constexpr (kWavePerFace<NFP, EPB>) {
-        // p = 7: wave-uniform tasks (component, face of direction d), component 4 the FP64 mass
-        const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
-        for (int k = wv; k < 10; k += NS / 64) {
-          const int v = k >> 1, f = 2 * d + (k & 1);
-          if (v < 4)
-            sJ[v * NF + f * NFP + lane] -= face_sum_uniform<N>(f, lane % N, lane / N, &sF[v * NS], ops.lm, ops.lp);
-          else
-            sJm[f * NFP + lane] -= face_sum_uniform<N>(f, lane % N, lane / N, sM, opsd.lm, opsd.lp);
-        }
-      } else
-      for (int fp = t; fp < 2 * NFP; fp += NS) {
-        const int f = 2 * d + fp / NFP, kk = fp % NFP;
-        const int a = kk % N, b = kk / N;
-        const bool hi = f & 1;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          float acc = 0;
-#pragma unroll
-          for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS32(P)>(hi, ops.lm, ops.lp, c) * sF[v * NS + line_pt<N>(d, c, a, b)];
-          sJ[v * NF + f * NFP + kk] -= acc;
-        }
-        double acc = 0;
-#pragma unroll
-        for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS32(P)>(hi, opsd.lm, opsd.lp, c) * sM[line_pt<N>(d, c, a, b)];
-        sJm[f * NFP + kk] -= acc;
-      }
-    }
-    __syncthreads();
+    elem_sync<NS>();
     if (act) {
       const int u = d == 0 ? 1 : 0, w = d == 2 ? 1 : 2;
       const int kk = idx[u] + N * idx[w];
+      const int stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+      const int b0 = t - idx[d] * stride;
       const bool cpy = OPL && !(UNI2 && d == 2);
-      const float cL = cpy ? sOpf[N * N + idx[d]] : ops.gcL[idx[d]], cR = cpy ? sOpf[N * N + N + idx[d]] : ops.gcR[idx[d]];
+      {
+        float row[N];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) div[1 + v] += sJ[v * NF + (2 * d) * NFP + kk] * cL + sJ[v * NF + (2 * d + 1) * NFP + kk] * cR;
-      divm += sJm[(2 * d) * NFP + kk] * (cpy ? sOpd[N * N + idx[d]] : opsd.gcL[idx[d]]) + sJm[(2 * d + 1) * NFP + kk] * (cpy ? sOpd[N * N + N + idx[d]] : opsd.gcR[idx[d]]);
+        for (int c = 0; c < N; ++c) row[c] = cpy ? sOpf[idx[d] * N + c] : ops.D[idx[d] * N + c];
+        const float cL = cpy ? sOpf[oL + idx[d]] : ops.gcL[idx[d]], cR = cpy ? sOpf[oR + idx[d]] : ops.gcR[idx[d]];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          float acc = 0, lo = 0, hi = 0;
+#pragma unroll
+          for (int c = 0; c < N; ++c) {
+            const float x = sU[v * NS + b0 + c * stride];
+            acc = fma(row[c], x, acc);
+            lo = fma(ops.lm[c], x, lo);
+            hi = fma(ops.lp[c], x, hi);
+          }
+          const float jl = sJ[v * NF + (2 * d) * NFP + kk] - lo, jr = sJ[v * NF + (2 * d + 1) * NFP + kk] - hi;
+          div[1 + v] += acc;
+          div[1 + v] += fma(jl, cL, jr * cR);
+        }
+      }
+      double acc = sJm[(2 * d) * NFP + kk] * (cpy ? sOpd[idx[d]] : opsd.gcL[idx[d]]);
+      acc = fma(sJm[(2 * d + 1) * NFP + kk], cpy ? sOpd[N + idx[d]] : opsd.gcR[idx[d]], acc);
+#pragma unroll
+      for (int c = 0; c < N; ++c) acc = fma(cpy ? sOpd[2 * N + idx[d] * N + c] : opsd.W[idx[d] * N + c], sM[b0 + c * stride], acc);
+      divm += acc;
     }
   }
+  if (PRE) elem_sync<NS>();
   // the RK update; with PRE the stored state also goes to LDS at once as U' (nothing reads sU
-  // after the last direction's divergence), and its momentum is kept for the FP64 face values
+  // any more), and its momentum is kept for the FP64 face values
   double xm[3] = {0, 0, 0};
   if (act) {
     double Rv[5];
@@ -677,134 +640,78 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
   constexpr int VPC = (18 / N) < 5 ? (18 / N) : 5;
   constexpr int NCH = VISC ? (5 + VPC - 1) / VPC : 0;
   constexpr int NR = NCH > 3 ? NCH : 3;
-  constexpr int UNW = P >= 6 ? 1 : VPC;  // bounds the LDS loads in flight at high degree
-  // face point fp: its line along the face normal runs over [b0 + c * stride], c = 0..N-1
-  auto line = [&](int fp, int &f, int &kk, int &b0, int &stride) {
-    f = fp / NFP;
-    kk = fp - f * NFP;
-    const int a = kk % N, b = kk / N, d = f >> 1;
-    stride = d == 0 ? 1 : (d == 1 ? N : N * N);
-    b0 = d == 0 ? N * kk : (d == 1 ? a + N * N * b : kk);
+  float *dst = face32 + e * 6 * 20 * NFP;
+  double *dm = facem + e * 6 * 3 * NFP;
+  // broken gradient of the nv variables from v0 on to sJ[(ii * nv + w) * NS + t]
+  constexpr int VG = SP ? 5 : VPC;
+  float jb[9], iJb = 0;
+  auto load_metric = [&]() {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) jb[c] = MST ? sMetall[slot][c * NS + t] : geo32_again[(e * 10 + c) * NS + t];
+    iJb = MST ? sMetall[slot][9 * NS + t] : geo32_again[(e * 10 + 9) * NS + t];
   };
-  __syncthreads();
-  if (SP) {
-    // one pass: the momentum and the whole gradient to LDS, then items (group, face point) of
-    // independent sums: group 0 U', groups 1-3 d/dx_ii of the five variables (face slot
-    // 5 + ii * 5 + v, LDS sJ[(v * 3 + ii) * N_s]), the last group the FP64 momentum
-    constexpr int NGRP = VISC ? 5 : 2;
+  auto gradient = [&](int v0, int nv) {
+    float dU[3][VG];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+      const int b0 = t - idx[d] * stride;
+      const bool cpy = OPL && !(UNI2 && d == 2);
+      float row[N];
+#pragma unroll
+      for (int c = 0; c < N; ++c) row[c] = cpy ? sOpf[idx[d] * N + c] : ops.D[idx[d] * N + c];
+#pragma unroll
+      for (int w = 0; w < VG; ++w) {
+        float acc = 0;
+        if (w < nv) {
+#pragma unroll
+          for (int c = 0; c < N; ++c) acc = fma(row[c], sU[(v0 + w) * NS + b0 + c * stride], acc);
+        }
+        dU[d][w] = acc;
+      }
+    }
+#pragma unroll
+    for (int w = 0; w < VG; ++w) {
+      if (w < nv) {
+#pragma unroll
+        for (int ii = 0; ii < 3; ++ii) {
+          float g = dot3(jb[ii], dU[0][w], jb[3 + ii], dU[1][w], jb[6 + ii], dU[2][w]);
+          sJ[(ii * nv + w) * NS + t] = iJb * g;
+        }
+      }
+    }
+  };
+  elem_sync<NS>();
+  if constexpr (SP) {
+    // one pass: the momentum and the whole gradient to LDS, then the traces of everything
     if (act) {
 #pragma unroll
       for (int i = 0; i < 3; ++i) sM[i * NS + t] = xm[i];
       if (VISC) {
-        float jb[9];
-#pragma unroll
-        for (int c = 0; c < 9; ++c) jb[c] = MST ? sMetall[slot][c * NS + t] : geo32_again[(e * 10 + c) * NS + t];
-        const float iJb = MST ? sMetall[slot][9 * NS + t] : geo32_again[(e * 10 + 9) * NS + t];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-          float d0 = 0, d1 = 0, d2 = 0;
-#pragma unroll
-          for (int c = 0; c < N; ++c) {
-            d0 += (OPL ? sOpf[idx[0] * N + c] : ops.D[idx[0] * N + c]) * sU[v * NS + c + N * (idx[1] + N * idx[2])];
-            d1 += (OPL ? sOpf[idx[1] * N + c] : ops.D[idx[1] * N + c]) * sU[v * NS + idx[0] + N * (c + N * idx[2])];
-            d2 += (OPL && !UNI2 ? sOpf[idx[2] * N + c] : ops.D[idx[2] * N + c]) * sU[v * NS + idx[0] + N * (idx[1] + N * c)];
-          }
-#pragma unroll
-          for (int ii = 0; ii < 3; ++ii) sJ[(v * 3 + ii) * NS + t] = iJb * (jb[ii] * d0 + jb[3 + ii] * d1 + jb[6 + ii] * d2);
-        }
+        load_metric();
+        gradient(0, 5);
       }
     }
-    __syncthreads();
-    if constexpr (FR_TAIL_PER_POINT32(P)) {
-      // whole face points per thread: each point's line and interpolation weights once, then
-      // every group; the same sums as the items below
-      for (int fp = t; act && fp < NF; fp += NS) {
-        int f, kk, b0, stride;
-        line(fp, f, kk, b0, stride);
-        const bool hi = f & 1;
-        float cf[N];
-        double cd[N];
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-          cf[c] = pick_end<FR_SCALAR_ENDS32(P)>(hi, ops.lm, ops.lp, c);
-          cd[c] = pick_end<FR_SCALAR_ENDS32(P)>(hi, opsd.lm, opsd.lp, c);
-        }
-#pragma unroll
-        for (int grp = 0; grp < NGRP - 1; ++grp) {
-#pragma unroll
-          for (int v = 0; v < 5; ++v) {
-            const float *src = grp == 0 ? &sU[v * NS] : &sJ[(v * 3 + grp - 1) * NS];
-            float acc = 0;
-#pragma unroll
-            for (int c = 0; c < N; ++c) acc += cf[c] * src[b0 + c * stride];
-            face_store<NFP>(acc, &face32[((e * 6 + f) * 20 + 5 * grp + v) * NFP + kk]);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          double acc = 0;
-#pragma unroll
-          for (int c = 0; c < N; ++c) acc += cd[c] * sM[i * NS + b0 + c * stride];
-          face_store<NFP>(acc, &facem[((e * 6 + f) * 3 + i) * NFP + kk]);
-        }
-      }
-      return;
-    }
+    elem_sync<NS>();
     if (act) {
-      for (int q = t; q < NGRP * NF; q += NS) {
-        const int grp = q / NF;
-        int f, kk, b0, stride;
-        line(q - grp * NF, f, kk, b0, stride);
-        const bool hi = f & 1;
-        if (grp == NGRP - 1) {
-#pragma unroll
-          for (int i = 0; i < 3; ++i) {
-            double acc = 0;
-#pragma unroll
-            for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS32(P)>(hi, opsd.lm, opsd.lp, c) * sM[i * NS + b0 + c * stride];
-            face_store<NFP>(acc, &facem[((e * 6 + f) * 3 + i) * NFP + kk]);
-          }
-        } else {
-#pragma unroll
-          for (int v = 0; v < 5; ++v) {
-            const float *src = grp == 0 ? &sU[v * NS] : &sJ[(v * 3 + grp - 1) * NS];
-            float acc = 0;
-#pragma unroll
-            for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS32(P)>(hi, ops.lm, ops.lp, c) * src[b0 + c * stride];
-            face_store<NFP>(acc, &face32[((e * 6 + f) * 20 + 5 * grp + v) * NFP + kk]);
-          }
-        }
-      }
+      write_traces<N, VISC ? 20 : 5, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
+      write_traces<N, 3, 1>(t, sM, opsd.lm, opsd.lp, dm, 3, [](int v) { return v; });
     }
     return;
   }
-  // p = 7: the face loops as wave-uniform tasks (value, face), 64 face points per task
+  // p = 7: wave-uniform tasks (array, direction), the direction's 64 lines on the lanes
+  static_assert(SP || !PRE || WPF, "above p = 6 the tail's tasks are wavefronts");
   const int lane = t & 63, wv = WPF ? __builtin_amdgcn_readfirstlane(t >> 6) : 0;
   const int la = lane % N, lb = lane / N;
+  auto task = [&](const float *src, int d, int val) {
+    float lo, hi;
+    face_sums_uniform<N, true>(d, la, lb, src, ops.lm, ops.lp, lo, hi, sRot);
+    face_store<NFP>(lo, &dst[(2 * d * 20 + val) * NFP + lane]);
+    face_store<NFP>(hi, &dst[((2 * d + 1) * 20 + val) * NFP + lane]);
+  };
   if (act) {
-    if constexpr (WPF) {
-      for (int k = wv; k < 5 * 6; k += NS / 64) {
-        const int v = k / 6, f = k - 6 * v;
-        face_store<NFP>(face_sum_uniform<N, true>(f, la, lb, &sU[v * NS], ops.lm, ops.lp, sRot),
-                        &face32[((e * 6 + f) * 20 + v) * NFP + lane]);
-      }
-    } else
-    for (int q = t; q < 5 * NF; q += NS) {
-      const int v = q / NF;
-      int f, kk, b0, stride;
-      line(q - v * NF, f, kk, b0, stride);
-      const bool hi = f & 1;
-      float acc = 0;
-#pragma unroll
-      for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS32(P)>(hi, ops.lm, ops.lp, c) * sU[v * NS + b0 + c * stride];
-      face_store<NFP>(acc, &face32[((e * 6 + f) * 20 + v) * NFP + kk]);
-    }
-  }
-  float jb[9], iJb = 0;
-  if (VISC && act) {
-#pragma unroll
-    for (int c = 0; c < 9; ++c) jb[c] = MST ? sMetall[slot][c * NS + t] : geo32_again[(e * 10 + c) * NS + t];
-    iJb = MST ? sMetall[slot][9 * NS + t] : geo32_again[(e * 10 + 9) * NS + t];
+    for (int k = wv; k < 5 * 3; k += NS / 64) task(sU + (k / 3) * NS, k % 3, k / 3);
+    if (VISC) load_metric();
   }
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
@@ -812,64 +719,24 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
     const int nv = r < NCH ? (5 - v0 < VPC ? 5 - v0 : VPC) : 0;
     if (act) {
       if (r < 3) sM[t] = xm[r];
-      if (VISC) {
-#pragma unroll UNW
-        for (int w = 0; w < VPC; ++w) {
-          if (w < nv) {
-            const int v = v0 + w;
-            float d0 = 0, d1 = 0, d2 = 0;
-#pragma unroll
-            for (int c = 0; c < N; ++c) {
-              d0 += (OPL ? sOpf[idx[0] * N + c] : ops.D[idx[0] * N + c]) * sU[v * NS + c + N * (idx[1] + N * idx[2])];
-              d1 += (OPL ? sOpf[idx[1] * N + c] : ops.D[idx[1] * N + c]) * sU[v * NS + idx[0] + N * (c + N * idx[2])];
-              d2 += (OPL && !UNI2 ? sOpf[idx[2] * N + c] : ops.D[idx[2] * N + c]) * sU[v * NS + idx[0] + N * (idx[1] + N * c)];
-            }
-#pragma unroll
-            for (int ii = 0; ii < 3; ++ii) sJ[(w * 3 + ii) * NS + t] = iJb * (jb[ii] * d0 + jb[3 + ii] * d1 + jb[6 + ii] * d2);
-          }
-        }
-      }
+      if (VISC && nv > 0) gradient(v0, nv);
     }
-    __syncthreads();
-    if (act && WPF) {
-      for (int k = wv; k < (r < 3 ? 6 : 0) + 3 * nv * 6; k += NS / 64) {
-        if (r < 3 && k < 6) {
-          face_store<NFP>(face_sum_uniform<N, true>(k, la, lb, sM, opsd.lm, opsd.lp, sRotd),
-                          &facem[((e * 6 + k) * 3 + r) * NFP + lane]);
+    elem_sync<NS>();
+    if (act) {
+      for (int k = wv; k < (r < 3 ? 3 : 0) + 9 * nv; k += NS / 64) {
+        if (r < 3 && k < 3) {
+          double lo, hi;
+          face_sums_uniform<N, true>(k, la, lb, sM, opsd.lm, opsd.lp, lo, hi, sRotd);
+          face_store<NFP>(lo, &dm[(2 * k * 3 + r) * NFP + lane]);
+          face_store<NFP>(hi, &dm[((2 * k + 1) * 3 + r) * NFP + lane]);
           continue;
         }
-        const int kg = r < 3 ? k - 6 : k;
-        const int ci = kg / 6, f = kg - 6 * ci;
-        const int v = v0 + ci / 3, ii = ci - (ci / 3) * 3;
-        face_store<NFP>(face_sum_uniform<N, true>(f, la, lb, &sJ[ci * NS], ops.lm, ops.lp, sRot),
-                        &face32[((e * 6 + f) * 20 + 5 + ii * 5 + v) * NFP + lane]);
+        const int kg = r < 3 ? k - 3 : k;
+        const int ci = kg / 3, d = kg - 3 * ci;
+        task(sJ + ci * NS, d, 5 + (ci / nv) * 5 + v0 + ci % nv);
       }
     }
-    if (act && !WPF) {
-      if (r < 3) {
-        for (int fp = t; fp < NF; fp += NS) {
-          int f, kk, b0, stride;
-          line(fp, f, kk, b0, stride);
-          const bool hi = f & 1;
-          double acc = 0;
-#pragma unroll
-          for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS32(P)>(hi, opsd.lm, opsd.lp, c) * sM[b0 + c * stride];
-          face_store<NFP>(acc, &facem[((e * 6 + f) * 3 + r) * NFP + kk]);
-        }
-      }
-      for (int q = t; q < 3 * nv * NF; q += NS) {
-        const int ci = q / NF;
-        const int v = v0 + ci / 3, ii = ci - (ci / 3) * 3;
-        int f, kk, b0, stride;
-        line(q - ci * NF, f, kk, b0, stride);
-        const bool hi = f & 1;
-        float acc = 0;
-#pragma unroll
-        for (int c = 0; c < N; ++c) acc += pick_end<FR_SCALAR_ENDS32(P)>(hi, ops.lm, ops.lp, c) * sJ[ci * NS + b0 + c * stride];
-        face_store<NFP>(acc, &face32[((e * 6 + f) * 20 + 5 + ii * 5 + v) * NFP + kk]);
-      }
-    }
-    __syncthreads();
+    elem_sync<NS>();
   }
 }
 
@@ -898,6 +765,8 @@ void ops_of(const DeviceMesh &dm, OpsT<float> &ops, OpsT<double> &opsd) {
   for (int i = 0; i < kMaxN * kMaxN; ++i) {
     ops.D[i] = float(dm.ops.D[i]);
     opsd.D[i] = dm.ops.D[i];
+    ops.W[i] = float(dm.ops.W[i]);
+    opsd.W[i] = dm.ops.W[i];
   }
   for (int i = 0; i < kMaxN; ++i) {
     ops.lm[i] = float(dm.ops.lm[i]);
