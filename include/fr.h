@@ -429,9 +429,9 @@ int fr_mlp_train_step(fr_mlp_t net, const float *X, int64_t n, int64_t ldx, cons
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight training or
  * serving loops, harnesses that forbid hipMalloc): fr_mlp_train_step with the same arguments,
- * kernels and results, bit for bit, but its per-sample activations, deltas and gradient partial
- * sums live in a fixed scratch array (14.2 MiB) that the library holds on each GPU it runs on
- * until the process ends, instead of buffers the network grows with hipMalloc. Nothing is
+ * kernels and results, bit for bit, but its partial sums of the gradient live in a fixed scratch
+ * array (12.3 MiB) that the library holds on each GPU it runs on until the process ends, instead of
+ * a buffer the network grows with hipMalloc. Nothing is
  * allocated or freed. n must be 1..FR_MLP_NOALLOC_MAX_N (FR_ERR_ARG beyond). Every call on one GPU
  * shares that GPU's array and overwrites it: calls that overlap in time on one GPU (other
  * streams, threads or networks) race and must be ordered by the caller. Enqueued on the

@@ -1,21 +1,22 @@
 // fr_mlp.hip -- the per-element network of the learned eddy-viscosity closure on gfx950.
 //
-// Forward and backward passes run one wavefront per 16 samples on the matrix cores
-// (v_mfma_f32_16x16x16_bf16, float32 accumulation). With that instruction a wave holds the
-// 16x16 result tile D[m][n] as lane (g = lane/16, c = lane%16) -> rows 4g..4g+3 of column c,
-// which is exactly the lane layout of its B operand (rows k = 4g..4g+3 of column c). A layer's
-// output tile t therefore feeds the next layer's K-step t without any data movement, and a
-// sample's 64 hidden values stay in the registers of the four lanes that share its column.
+// Forward and backward passes run four wavefronts per 16 samples on the matrix cores
+// (v_mfma_f32_16x16x16_bf16, float32 accumulation), each wave a 16-unit block of every layer's
+// output. With that instruction a wave holds the 16x16 result tile D[m][n] as lane (g = lane/16,
+// c = lane%16) -> rows 4g..4g+3 of column c, which is the lane layout of its B operand (rows k =
+// 4g..4g+3 of column c): a layer's output goes to the next through LDS as [sample][unit], four
+// units per 16-byte access.
 //
 // Weights are the bfloat16 roundings of float32 masters. An activation x enters a product as
 // hi + lo, hi = bf16(x), lo = bf16(x - hi) (two MFMAs), which represents it to 2^-17 relative,
 // so the products see the weights exactly and the activations nearly exactly.
 //
-// Training: a per-sample pass writes the activations and back-propagated deltas; a second
-// kernel reduces the weight gradients over samples (dW = delta^T h on the matrix cores with
-// hi/lo splits of both operands: hi*hi + hi*lo + lo*hi) into per-split partial sums; the Adam
-// kernel adds the partials in a fixed order and updates the masters and their bf16 copies.
-// There are no atomics: every result is deterministic.
+// Training: after the backward pass each wave adds the 16 samples' outer products to its rows of
+// the weight gradients on the matrix cores (dW = delta^T h with both operands split: hi*hi + hi*lo +
+// lo*hi), which it keeps in registers over all of the block's samples and writes as one partial sum
+// per block. The Adam kernel adds the partials in a fixed
+// order and updates the masters and their bf16 copies. There are no atomics: every result is
+// deterministic.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -34,7 +35,8 @@ namespace {
 
 constexpr int H = 64;         // hidden units per layer
 constexpr int kMaxIn = 128;   // inputs (padded to a multiple of 16)
-constexpr int kSplit = 256;   // samples per partial sum of the weight gradients
+constexpr int kChunk = 16;    // samples a block takes at a time
+constexpr int kMaxPart = 256; // blocks of the training pass, each with a partial sum of the gradient
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -76,10 +78,7 @@ struct Net {
   float *w3r = nullptr;      // [H] bf16-rounded w3 as float
   float *mean = nullptr;     // [FP] (0 beyond F)
   float *istd = nullptr;     // [FP] 1/std (0 beyond F)
-  // training scratch, per sample
-  int64_t cap = 0;
-  float *xh = nullptr, *h1 = nullptr, *h2 = nullptr, *d1 = nullptr, *d2 = nullptr, *dz = nullptr, *sq = nullptr;
-  float *part = nullptr;     // [splits][np + 1]
+  float *part = nullptr;     // training scratch: [blocks][np + 1] partial gradients and losses
   int64_t part_cap = 0;
   float *grad = nullptr;     // [np]
   float *dloss = nullptr;    // [1]
@@ -90,218 +89,267 @@ struct NetArgs {
   int F, FP;
   const unsigned short *W1b, *W2b, *W2Tb;
   const float *b1, *b2, *w3r, *b3, *mean, *istd;
+  // offsets of the parameters in a partial gradient (training)
+  int64_t np, oW1, ob1, oW2, ob2, ow3, ob3;
 };
 
 // ------------------------------------------------------------------------------------------
-// Forward pass (TRAIN: also the loss terms and the back-propagated deltas), 4 waves per block,
-// 16 samples per wave.
+// Forward pass of 16 samples per block, a quarter of each layer's units per wave; TRAIN: also the
+// loss, the back-propagated deltas and this block's share of the gradient.
+//
+// A pass over a few thousand samples is bound by the instructions one wave issues in turn (splits,
+// tanh): with a wave for all 64 units of 16 samples, 4096 samples kept one SIMD in four busy.
+// Each wave keeps its rows of the weights in registers. 4096 samples of 68 inputs (us): evaluation
+// 10.6 -> 4.9; training pass 20.4 and a separate gradient kernel 67.5 -> 12.5 for both.
 // ------------------------------------------------------------------------------------------
-template <int KT, bool TRAIN>
-__global__ __launch_bounds__(256) void k_mlp(NetArgs a, const float *__restrict__ X, int64_t n, int64_t ldx,
-                                             float *__restrict__ y, double *__restrict__ nu, double nu_scale,
-                                             const float *__restrict__ tgt, float inv_n, float *__restrict__ xh,
-                                             float *__restrict__ h1o, float *__restrict__ h2o,
-                                             float *__restrict__ d1o, float *__restrict__ d2o,
-                                             float *__restrict__ dzo, float *__restrict__ sqo) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane >> 4, c = lane & 15;
-  const int64_t s = ((int64_t)blockIdx.x * 4 + wave) * 16 + c;  // this lane's sample
-  const bool ok = s < n;
-
-  // standardised inputs, B layout of K-step kk: rows k = 16 kk + 4 g + i, column = sample
-  float xr[KT][4];
+// A value in the products: its hi and lo halves in one word.
+__device__ __forceinline__ unsigned pack_hl(float x) {
+  const unsigned short h = bf16_bits(x);
+  return (unsigned)h | ((unsigned)bf16_bits(x - bf16_val(h)) << 16);
+}
+__device__ __forceinline__ void unpack_hl(const unsigned u[4], v4s &hi, v4s &lo) {
 #pragma unroll
-  for (int kk = 0; kk < KT; ++kk)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = 16 * kk + 4 * g + i;
-      xr[kk][i] = (ok && k < a.F) ? (X[s * ldx + k] - a.mean[k]) * a.istd[k] : 0.f;
-    }
-  if (TRAIN && ok) {
-#pragma unroll
-    for (int kk = 0; kk < KT; ++kk)
-      *(float4 *)&xh[s * a.FP + 16 * kk + 4 * g] = make_float4(xr[kk][0], xr[kk][1], xr[kk][2], xr[kk][3]);
-  }
-  // layer 1
-  float h1[4][4];
-  {
-    v4s bh[KT], bl[KT];
-#pragma unroll
-    for (int kk = 0; kk < KT; ++kk) split4(xr[kk], bh[kk], bl[kk]);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      v4f acc;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = a.b1[16 * t + 4 * g + i];
-#pragma unroll
-      for (int kk = 0; kk < KT; ++kk) {
-        const v4s w = *(const v4s *)&a.W1b[(16 * t + c) * a.FP + 16 * kk + 4 * g];
-        acc = mfma(w, bh[kk], acc);
-        acc = mfma(w, bl[kk], acc);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) h1[t][i] = tanhf(acc[i]);
-    }
-  }
-  // layer 2
-  float h2[4][4];
-  {
-    v4s bh[4], bl[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) split4(h1[t], bh[t], bl[t]);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      v4f acc;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = a.b2[16 * t + 4 * g + i];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const v4s w = *(const v4s *)&a.W2b[(16 * t + c) * H + 16 * kk + 4 * g];
-        acc = mfma(w, bh[kk], acc);
-        acc = mfma(w, bl[kk], acc);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) h2[t][i] = tanhf(acc[i]);
-    }
-  }
-  // output unit: the four lanes of a column hold its 64 values; reduce over g
-  float z = 0.f;
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) z += a.w3r[16 * t + 4 * g + i] * h2[t][i];
-  z += __shfl_xor(z, 16);
-  z += __shfl_xor(z, 32);
-  z += a.b3[0];
-  const float yv = softplus(z);
-  if (!TRAIN) {
-    if (ok && g == 0) {
-      if (y) y[s] = yv;
-      if (nu) nu[s] = nu_scale * (double)yv;
-    }
-    return;
-  }
-  // loss terms and dL/dz = 2 (y - t) / n * softplus'(z)
-  const float r = ok ? yv - tgt[s] : 0.f;
-  const float dz = ok ? 2.f * r * inv_n * logistic(z) : 0.f;
-  if (ok && g == 0) {
-    if (y) y[s] = yv;
-    dzo[s] = dz;
-    sqo[s] = r * r;
-  }
-  // delta2 = dz w3 (1 - h2^2), D layout
-  float d2[4][4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) d2[t][i] = dz * a.w3r[16 * t + 4 * g + i] * (1.f - h2[t][i] * h2[t][i]);
-  // delta1 = (W2^T delta2) (1 - h1^2)
-  float d1[4][4];
-  {
-    v4s bh[4], bl[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) split4(d2[t], bh[t], bl[t]);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      v4f acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const v4s w = *(const v4s *)&a.W2Tb[(16 * t + c) * H + 16 * kk + 4 * g];
-        acc = mfma(w, bh[kk], acc);
-        acc = mfma(w, bl[kk], acc);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) d1[t][i] = acc[i] * (1.f - h1[t][i] * h1[t][i]);
-    }
-  }
-  if (ok) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int64_t o = s * H + 16 * t + 4 * g;
-      *(float4 *)&h1o[o] = make_float4(h1[t][0], h1[t][1], h1[t][2], h1[t][3]);
-      *(float4 *)&h2o[o] = make_float4(h2[t][0], h2[t][1], h2[t][2], h2[t][3]);
-      *(float4 *)&d1o[o] = make_float4(d1[t][0], d1[t][1], d1[t][2], d1[t][3]);
-      *(float4 *)&d2o[o] = make_float4(d2[t][0], d2[t][1], d2[t][2], d2[t][3]);
-    }
+  for (int i = 0; i < 4; ++i) {
+    hi[i] = (short)(u[i] & 0xffffu);
+    lo[i] = (short)(u[i] >> 16);
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// Weight-gradient partial sums over split blockIdx.y (samples [y*kSplit, (y+1)*kSplit) ∩ [0,n)).
-// One wave per job: jobs 0..4KT-1 are 16x16 tiles of dW1 = sum_s delta1_s xh_s^T, the next 16
-// tiles of dW2 = sum_s delta2_s h1_s^T, then db1, db2, dw3 and (db3, loss).
-// ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_mlp_wgrad(int F, int FP, int KT, int64_t n, const float *__restrict__ xh,
-                                                  const float *__restrict__ h1, const float *__restrict__ h2,
-                                                  const float *__restrict__ d1, const float *__restrict__ d2,
-                                                  const float *__restrict__ dz, const float *__restrict__ sq,
-                                                  int64_t np, int64_t oW1, int64_t ob1, int64_t oW2, int64_t ob2,
-                                                  int64_t ow3, int64_t ob3, float inv_n, float *__restrict__ part) {
-  const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-  const int job = blockIdx.x;
-  const int64_t s0 = (int64_t)blockIdx.y * kSplit;
-  const int64_t s1 = s0 + kSplit < n ? s0 + kSplit : n;
-  float *out = part + (int64_t)blockIdx.y * (np + 1);
-  const int nW1 = 4 * KT;
-  if (job < nW1 + 16) {
-    // tile (row block tm, column block tn) of dW = sum_s A_s B_s^T with A = delta (64 rows)
-    // and B = xh or h1; MFMA K runs over samples: A-operand lane (g, c) needs
-    // delta[s0 + 4g + i][16 tm + c], B-operand lane needs B[s0 + 4g + i][16 tn + c]
-    const bool w1 = job < nW1;
-    const int tm = w1 ? job / KT : (job - nW1) / 4;
-    const int tn = w1 ? job % KT : (job - nW1) % 4;
-    const float *A = w1 ? d1 : d2;
-    const float *B = w1 ? xh : h1;
-    const int ldb = w1 ? FP : H;
-    v4f acc = {0.f, 0.f, 0.f, 0.f};
-    for (int64_t sb = s0; sb < s1; sb += 16) {
-      float av[4], bv[4];
+// Sum over the 16 lanes of a row, on every one of them (rotations within the row).
+template <int R>
+__device__ __forceinline__ float row_ror(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 | R, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row_sum(float x) {
+  x += row_ror<8>(x);
+  x += row_ror<4>(x);
+  x += row_ror<2>(x);
+  return x + row_ror<1>(x);
+}
+
+// Row strides in LDS: 16-byte aligned, and lanes of different rows on different banks.
+constexpr int kRowH = H + 4;
+
+// Four consecutive entries of a packed row (a B operand's four rows of one sample).
+__device__ __forceinline__ void operand(const unsigned *row, v4s &hi, v4s &lo) {
+  const uint4 w = *(const uint4 *)row;
+  const unsigned u[4] = {w.x, w.y, w.z, w.w};
+  unpack_hl(u, hi, lo);
+}
+// One unit's entries of samples 4 g .. 4 g + 3: an operand whose K runs over the samples.
+template <int ROW>
+__device__ __forceinline__ void operand_samples(const unsigned *tab, int g, int unit, v4s &hi, v4s &lo) {
+  unsigned u[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int64_t s = sb + 4 * g + i;
-        av[i] = s < s1 ? A[s * H + 16 * tm + c] : 0.f;
-        bv[i] = s < s1 ? B[s * ldb + 16 * tn + c] : 0.f;
+  for (int i = 0; i < 4; ++i) u[i] = tab[(4 * g + i) * ROW + unit];
+  unpack_hl(u, hi, lo);
+}
+__device__ __forceinline__ void put4(unsigned *row, const float x[4]) {
+  *(uint4 *)row = make_uint4(pack_hl(x[0]), pack_hl(x[1]), pack_hl(x[2]), pack_hl(x[3]));
+}
+
+template <int KT, bool TRAIN>
+__global__ __launch_bounds__(256) void k_mlp(NetArgs a, const float *__restrict__ X, int64_t n, int64_t ldx,
+                                             float *__restrict__ y, double *__restrict__ nu, double nu_scale,
+                                             const float *__restrict__ tgt, float inv_n, float *__restrict__ part) {
+  constexpr int FP = 16 * KT, kRowX = FP + 4;
+  // the samples' inputs, activations and deltas, [sample][unit] (packed; sZ: h2 as floats)
+  __shared__ alignas(16) unsigned sX[kChunk * kRowX];
+  __shared__ alignas(16) unsigned sH1[kChunk * kRowH];
+  __shared__ alignas(16) float sZ[kChunk * kRowH];
+  __shared__ alignas(16) unsigned sD2[TRAIN ? kChunk * kRowH : 4];
+  __shared__ alignas(16) unsigned sD1[TRAIN ? kChunk * kRowH : 4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, c = lane & 15;
+  const int u0 = 16 * wave + 4 * g;  // this lane's four units of its wave's block
+  // this wave's rows of the weights (A operands), biases and output weights
+  v4s w1[KT], w2[4], w2t[4];
+#pragma unroll
+  for (int kk = 0; kk < KT; ++kk) w1[kk] = *(const v4s *)&a.W1b[(16 * wave + c) * FP + 16 * kk + 4 * g];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    w2[kk] = *(const v4s *)&a.W2b[(16 * wave + c) * H + 16 * kk + 4 * g];
+    if (TRAIN) w2t[kk] = *(const v4s *)&a.W2Tb[(16 * wave + c) * H + 16 * kk + 4 * g];
+  }
+  const float4 b1 = *(const float4 *)&a.b1[u0], b2 = *(const float4 *)&a.b2[u0];
+  float w3[4][4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const float4 q = *(const float4 *)&a.w3r[16 * t + 4 * g];
+    w3[t][0] = q.x;
+    w3[t][1] = q.y;
+    w3[t][2] = q.z;
+    w3[t][3] = q.w;
+  }
+  const float4 w3o = *(const float4 *)&a.w3r[u0];
+  const float w3u[4] = {w3o.x, w3o.y, w3o.z, w3o.w};
+  const float b3 = a.b3[0];
+  // rows of whole 16-byte groups are read with 16-byte loads
+  const bool vec = (ldx & 3) == 0 && ((uintptr_t)X & 15) == 0;
+  v4f gW1[TRAIN ? KT : 1], gW2[TRAIN ? 4 : 1];  // gradient tiles: row block `wave`, every column block
+  float vd1[4] = {0.f, 0.f, 0.f, 0.f}, vd2[4] = {0.f, 0.f, 0.f, 0.f}, vw3[4] = {0.f, 0.f, 0.f, 0.f};
+  float vz = 0.f, vl = 0.f;
+  if (TRAIN) {
+#pragma unroll
+    for (int t = 0; t < KT; ++t) gW1[t] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) gW2[t] = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int64_t chunk = blockIdx.x; chunk * kChunk < n; chunk += gridDim.x) {
+    const int64_t s = chunk * kChunk + c;  // this lane's sample
+    const bool ok = s < n;
+    const float target = TRAIN && ok ? tgt[s] : 0.f;
+    // standardised inputs, K-steps shared out over the waves: rows k = 16 kk + 4 g + i
+#pragma unroll
+    for (int kk = wave; kk < KT; kk += 4) {
+      const int k0 = 16 * kk + 4 * g;
+      float x[4] = {0.f, 0.f, 0.f, 0.f};
+      if (vec && ok && k0 + 3 < a.F) {
+        const float4 q = *(const float4 *)&X[s * ldx + k0];
+        x[0] = q.x;
+        x[1] = q.y;
+        x[2] = q.z;
+        x[3] = q.w;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (ok && k0 + i < a.F) x[i] = X[s * ldx + k0 + i];
       }
-      v4s ah, al, bh, bl;
-      split4(av, ah, al);
-      split4(bv, bh, bl);
-      acc = mfma(ah, bh, acc);
-      acc = mfma(ah, bl, acc);
-      acc = mfma(al, bh, acc);
+      const float4 mu = *(const float4 *)&a.mean[k0], is = *(const float4 *)&a.istd[k0];
+      const float m4[4] = {mu.x, mu.y, mu.z, mu.w}, i4[4] = {is.x, is.y, is.z, is.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = (ok && k0 + i < a.F) ? (x[i] - m4[i]) * i4[i] : 0.f;
+      put4(&sX[c * kRowX + k0], x);
     }
-    // D[m][k]: lane holds rows 16 tm + 4g + i, column 16 tn + c
+    __syncthreads();
+    // layer 1
+    float h1[4], h2[4];
+    {
+      v4f acc = {b1.x, b1.y, b1.z, b1.w};
+#pragma unroll
+      for (int kk = 0; kk < KT; ++kk) {
+        v4s bh, bl;
+        operand(&sX[c * kRowX + 16 * kk + 4 * g], bh, bl);
+        acc = mfma(w1[kk], bh, acc);
+        acc = mfma(w1[kk], bl, acc);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) h1[i] = tanhf(acc[i]);
+    }
+    put4(&sH1[c * kRowH + u0], h1);
+    __syncthreads();
+    // layer 2
+    {
+      v4f acc = {b2.x, b2.y, b2.z, b2.w};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        v4s bh, bl;
+        operand(&sH1[c * kRowH + 16 * kk + 4 * g], bh, bl);
+        acc = mfma(w2[kk], bh, acc);
+        acc = mfma(w2[kk], bl, acc);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) h2[i] = tanhf(acc[i]);
+    }
+    *(float4 *)&sZ[c * kRowH + u0] = make_float4(h2[0], h2[1], h2[2], h2[3]);
+    __syncthreads();
+    if (!TRAIN && wave > 0) continue;  // (every wave meets every barrier of every chunk)
+    // output unit: lane (g, c) adds units 16 t + 4 g + i, then the four lanes of a column
+    float z = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float4 q = *(const float4 *)&sZ[c * kRowH + 16 * t + 4 * g];
+      z += w3[t][0] * q.x;
+      z += w3[t][1] * q.y;
+      z += w3[t][2] * q.z;
+      z += w3[t][3] * q.w;
+    }
+    z += __shfl_xor(z, 16);
+    z += __shfl_xor(z, 32);
+    z += b3;
+    const float yv = softplus(z);
+    if (!TRAIN) {
+      if (ok && g == 0) {
+        if (y) y[s] = yv;
+        if (nu) nu[s] = nu_scale * (double)yv;
+      }
+      continue;
+    }
+    // loss terms and dL/dz = 2 (y - t) / n * softplus'(z)
+    const float r = ok ? yv - target : 0.f;
+    const float dz = ok ? 2.f * r * inv_n * logistic(z) : 0.f;
+    // delta2 = dz w3 (1 - h2^2)
+    float d2[4], d1[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d2[i] = dz * w3u[i] * (1.f - h2[i] * h2[i]);
+    put4(&sD2[c * kRowH + u0], d2);
+    __syncthreads();
+    // delta1 = (W2^T delta2) (1 - h1^2)
+    {
+      v4f acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        v4s bh, bl;
+        operand(&sD2[c * kRowH + 16 * kk + 4 * g], bh, bl);
+        acc = mfma(w2t[kk], bh, acc);
+        acc = mfma(w2t[kk], bl, acc);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) d1[i] = acc[i] * (1.f - h1[i] * h1[i]);
+    }
+    put4(&sD1[c * kRowH + u0], d1);
+    // bias and output-weight sums over the 16 samples, on every lane of a row
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int m = 16 * tm + 4 * g + i, k = 16 * tn + c;
-      if (w1) {
-        if (k < F) out[oW1 + (int64_t)m * F + k] = acc[i];
-      } else {
-        out[oW2 + (int64_t)m * H + k] = acc[i];
-      }
+      vd1[i] += row_sum(d1[i]);
+      vd2[i] += row_sum(d2[i]);
+      vw3[i] += row_sum(dz * h2[i]);
     }
-    return;
-  }
-  const int v = job - nW1 - 16;  // 0 db1, 1 db2, 2 dw3, 3 (db3, loss)
-  if (v < 3) {
-    const float *src = v == 0 ? d1 : (v == 1 ? d2 : h2);
-    float acc = 0.f;
-    for (int64_t s = s0; s < s1; ++s) acc += (v == 2 ? dz[s] : 1.f) * src[s * H + lane];
-    out[(v == 0 ? ob1 : (v == 1 ? ob2 : ow3)) + lane] = acc;
-  } else {
-    float a = 0.f, b = 0.f;
-    for (int64_t s = s0 + lane; s < s1; s += 64) {
-      a += dz[s];
-      b += sq[s];
-    }
+    vz += dz;
+    vl += r * r;
+    __syncthreads();
+    // weight gradients of the chunk: the matrix product's K runs over its 16 samples
+    v4s ah, al, bh, bl;
+    operand_samples<kRowH>(sD1, g, 16 * wave + c, ah, al);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      a += __shfl_xor(a, o);
-      b += __shfl_xor(b, o);
+    for (int t = 0; t < KT; ++t) {
+      operand_samples<kRowX>(sX, g, 16 * t + c, bh, bl);
+      gW1[t] = mfma(ah, bh, gW1[t]);
+      gW1[t] = mfma(ah, bl, gW1[t]);
+      gW1[t] = mfma(al, bh, gW1[t]);
     }
-    if (lane == 0) {
-      out[ob3] = a;
-      out[np] = b * inv_n;
+    operand_samples<kRowH>(sD2, g, 16 * wave + c, ah, al);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      operand_samples<kRowH>(sH1, g, 16 * t + c, bh, bl);
+      gW2[t] = mfma(ah, bh, gW2[t]);
+      gW2[t] = mfma(ah, bl, gW2[t]);
+      gW2[t] = mfma(al, bh, gW2[t]);
     }
+    __syncthreads();  // before the next chunk's samples
+  }
+  if (!TRAIN) return;
+  float *out = part + (int64_t)blockIdx.x * (a.np + 1);
+  // D[m][k]: lane holds rows 16 wave + 4 g + i, column 16 t + c
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = u0 + i;
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+      if (16 * t + c < a.F) out[a.oW1 + (int64_t)m * a.F + 16 * t + c] = gW1[t][i];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) out[a.oW2 + (int64_t)m * H + 16 * t + c] = gW2[t][i];
+    if (c == 0) {
+      out[a.ob1 + m] = vd1[i];
+      out[a.ob2 + m] = vd2[i];
+      out[a.ow3 + m] = vw3[i];
+    }
+  }
+  vz = row_sum(vz);
+  vl = row_sum(vl);
+  if (threadIdx.x == 0) {
+    out[a.ob3] = vz;
+    out[a.np] = vl * inv_n;
   }
 }
 
@@ -322,18 +370,33 @@ __device__ __forceinline__ void write_copies(int64_t i, float th, int F, int FP,
   }
 }
 
-// Sum the partials in split order; optionally export the gradient and the loss; optionally
-// take one Adam step and refresh the bf16 copies.
-__global__ __launch_bounds__(256) void k_mlp_adam(const float *__restrict__ part, int splits, int64_t np,
+// Sum the partials in a fixed order (each of kAdamWays threads a run of them, in double:
+// there are up to 256), eight loads in flight per thread;
+// optionally export the gradient and the loss; optionally take one Adam step and refresh the bf16
+// copies.
+constexpr int kAdamWays = 8;
+__global__ __launch_bounds__(64 * kAdamWays) void k_mlp_adam(const float *__restrict__ part, int parts, int64_t np,
                                                   float *__restrict__ grad, float *__restrict__ loss, int update,
                                                   float lr, float c1, float c2, float *__restrict__ theta,
                                                   float *__restrict__ am, float *__restrict__ av, int F, int FP,
                                                   int64_t oW1, int64_t oW2, int64_t ow3, unsigned short *W1b,
                                                   unsigned short *W2b, unsigned short *W2Tb, float *w3r) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i > np) return;
-  float gsum = 0.f;
-  for (int s = 0; s < splits; ++s) gsum += part[(int64_t)s * (np + 1) + i];
+  __shared__ double sum[kAdamWays][64];
+  const int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+  const int way = threadIdx.x >> 6, each = (parts + kAdamWays - 1) / kAdamWays;
+  const int from = way * each, to = from + each < parts ? from + each : parts;
+  double q = 0.0;
+  if (i <= np) {
+#pragma unroll 8
+    for (int s = from; s < to; ++s) q += part[(int64_t)s * (np + 1) + i];
+  }
+  sum[way][threadIdx.x & 63] = q;
+  __syncthreads();
+  if (way > 0 || i > np) return;
+  double total = 0.0;
+#pragma unroll
+  for (int w = 0; w < kAdamWays; ++w) total += sum[w][threadIdx.x];
+  const float gsum = (float)total;
   if (i == np) {
     if (loss) *loss = gsum;
     return;
@@ -391,40 +454,37 @@ NetArgs args_of(const Net &n) {
   a.b3 = n.theta + n.ob3;
   a.mean = n.mean;
   a.istd = n.istd;
+  a.np = n.np;
+  a.oW1 = n.oW1;
+  a.ob1 = n.ob1;
+  a.oW2 = n.oW2;
+  a.ob2 = n.ob2;
+  a.ow3 = n.ow3;
+  a.ob3 = n.ob3;
   return a;
 }
 
-// Per-sample training buffers (activations, deltas, loss terms) and the per-split partial sums of
-// the gradient: the network's own growing buffers, or a share of the fixed scratch array.
-struct TrainBufs {
-  float *xh = nullptr, *h1 = nullptr, *h2 = nullptr, *d1 = nullptr, *d2 = nullptr, *dz = nullptr, *sq = nullptr;
-  float *part = nullptr;
-};
+constexpr int64_t kMaxBlocks = 1 << 20;  // of an evaluation; blocks loop over the samples beyond
 
-TrainBufs net_bufs(const Net &n) {
-  TrainBufs b;
-  b.xh = n.xh;
-  b.h1 = n.h1;
-  b.h2 = n.h2;
-  b.d1 = n.d1;
-  b.d2 = n.d2;
-  b.dz = n.dz;
-  b.sq = n.sq;
-  b.part = n.part;
-  return b;
+// Blocks of the training pass over n samples: one per 16 samples up to a block per CU.
+constexpr int64_t train_parts(int64_t n) {
+  const int64_t chunks = (n + kChunk - 1) / kChunk;
+  return chunks < kMaxPart ? chunks : kMaxPart;
 }
 
+// part: the partial gradients of a training pass (the network's own or the fixed scratch array)
 template <bool TRAIN>
 int launch_mlp(const Net &net, hipStream_t st, const float *X, int64_t n, int64_t ldx, float *y, double *nu,
-               double nu_scale, const float *tgt, const TrainBufs &tb = TrainBufs()) {
+               double nu_scale, const float *tgt, float *part = nullptr) {
   const NetArgs a = args_of(net);
-  const unsigned blocks = (unsigned)((n + 63) / 64);
+  const int64_t chunks = (n + kChunk - 1) / kChunk;
+  const unsigned blocks = (unsigned)(TRAIN ? train_parts(n) : (chunks < kMaxBlocks ? chunks : kMaxBlocks));
   const float inv_n = 1.f / (float)n;
   switch (net.FP / 16) {
 #define CASE(K)                                                                                                  \
   case K:                                                                                                        \
     hipLaunchKernelGGL((k_mlp<K, TRAIN>), dim3(blocks), dim3(256), 0, st, a, X, n, ldx, y, nu, nu_scale, tgt,   \
-                       inv_n, tb.xh, tb.h1, tb.h2, tb.d1, tb.d2, tb.dz, tb.sq);                                   \
+                       inv_n, part);                                                                             \
     break;
     CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
 #undef CASE
@@ -435,56 +495,38 @@ int launch_mlp(const Net &net, hipStream_t st, const float *X, int64_t n, int64_
 }
 
 int ensure_scratch(Net &net, int64_t n) {
-  if (n > net.cap) {
-    for (float *p : {net.xh, net.h1, net.h2, net.d1, net.d2, net.dz, net.sq})
-      if (p) (void)hipFree(p);
-    const int64_t cap = n;
-    MCHK(hipMalloc(&net.xh, cap * net.FP * sizeof(float)));
-    MCHK(hipMalloc(&net.h1, cap * H * sizeof(float)));
-    MCHK(hipMalloc(&net.h2, cap * H * sizeof(float)));
-    MCHK(hipMalloc(&net.d1, cap * H * sizeof(float)));
-    MCHK(hipMalloc(&net.d2, cap * H * sizeof(float)));
-    MCHK(hipMalloc(&net.dz, cap * sizeof(float)));
-    MCHK(hipMalloc(&net.sq, cap * sizeof(float)));
-    net.cap = cap;
-  }
-  const int64_t splits = (n + kSplit - 1) / kSplit;
-  if (splits > net.part_cap) {
+  const int64_t parts = train_parts(n);
+  if (parts > net.part_cap) {
     if (net.part) (void)hipFree(net.part);
-    MCHK(hipMalloc(&net.part, splits * (net.np + 1) * sizeof(float)));
-    net.part_cap = splits;
+    net.part = nullptr;
+    net.part_cap = 0;
+    MCHK(hipMalloc(&net.part, parts * (net.np + 1) * sizeof(float)));
+    net.part_cap = parts;
   }
   return FR_OK;
 }
 
-// forward + backward + gradient reduction; then the Adam kernel (update or export only). fixed:
-// training buffers to use instead of the network's own (which are grown here otherwise).
+// forward + backward + gradient; then the Adam kernel (update or export only). fixed: training
+// scratch to use instead of the network's own (which is grown here otherwise).
 int grad_pass(fr_mlp_t m, const float *X, int64_t n, int64_t ldx, const float *t, bool update, float lr,
-              float *loss_dev, const TrainBufs *fixed = nullptr) {
+              float *loss_dev, float *fixed = nullptr) {
   Net &net = m->net;
   if (!X || !t || n <= 0 || ldx < net.F) return fr_fail(FR_ERR_ARG, "bad X / t / n / ldx");
   if (!fixed) {
     int rc = ensure_scratch(net, n);
     if (rc) return rc;
   }
-  const TrainBufs tb = fixed ? *fixed : net_bufs(net);
-  int rc = launch_mlp<true>(net, m->stream, X, n, ldx, nullptr, nullptr, 0.0, t, tb);
+  float *part = fixed ? fixed : net.part;
+  int rc = launch_mlp<true>(net, m->stream, X, n, ldx, nullptr, nullptr, 0.0, t, part);
   if (rc) return rc;
-  const int KT = net.FP / 16;
-  const int64_t splits = (n + kSplit - 1) / kSplit;
-  const int jobs = 4 * KT + 16 + 4;
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3(jobs, (unsigned)splits), dim3(64), 0, m->stream, net.F, net.FP, KT, n,
-                     tb.xh, tb.h1, tb.h2, tb.d1, tb.d2, tb.dz, tb.sq, net.np, net.oW1, net.ob1, net.oW2,
-                     net.ob2, net.ow3, net.ob3, 1.f / (float)n, tb.part);
-  MCHK(hipGetLastError());
   float c1 = 1.f, c2 = 1.f;
   if (update) {
     net.step += 1;
     c1 = (float)(1.0 / (1.0 - std::pow(0.9, net.step)));
     c2 = (float)(1.0 / (1.0 - std::pow(0.999, net.step)));
   }
-  hipLaunchKernelGGL(k_mlp_adam, dim3((unsigned)((net.np + 1 + 255) / 256)), dim3(256), 0, m->stream, tb.part,
-                     (int)splits, net.np, update ? nullptr : net.grad, loss_dev, update ? 1 : 0, lr, c1, c2,
+  hipLaunchKernelGGL(k_mlp_adam, dim3((unsigned)((net.np + 1 + 63) / 64)), dim3(64 * kAdamWays), 0, m->stream, part,
+                     (int)train_parts(n), net.np, update ? nullptr : net.grad, loss_dev, update ? 1 : 0, lr, c1, c2,
                      net.theta, net.am, net.av, net.F, net.FP, net.oW1, net.oW2, net.ow3, net.W1b, net.W2b,
                      net.W2Tb, net.w3r);
   MCHK(hipGetLastError());
@@ -506,16 +548,14 @@ int upload_params(fr_mlp_t m, const float *params) {
 
 void free_net(Net &n) {
   for (void *p : {(void *)n.theta, (void *)n.am, (void *)n.av, (void *)n.W1b, (void *)n.W2b, (void *)n.W2Tb,
-                  (void *)n.w3r, (void *)n.mean, (void *)n.istd, (void *)n.xh, (void *)n.h1, (void *)n.h2,
-                  (void *)n.d1, (void *)n.d2, (void *)n.dz, (void *)n.sq, (void *)n.part, (void *)n.grad,
-                  (void *)n.dloss})
+                  (void *)n.w3r, (void *)n.mean, (void *)n.istd, (void *)n.part, (void *)n.grad, (void *)n.dloss})
     if (p) (void)hipFree(p);
 }
 
 }  // namespace
 
 // ------------------------------------------------------------------------------------------
-// Training without allocation (fr_mlp_train_step_noalloc): the training buffers of one call live
+// Training without allocation (fr_mlp_train_step_noalloc): the partial gradients of one call live
 // in `scratch`, a fixed array each GPU holds for the life of the process, sized for
 // kNoAllocMaxN samples at the largest input count. Host code never passes the array's name to a
 // kernel (on the host it is only a stand-in for the symbol): each device's address comes from
@@ -525,13 +565,7 @@ namespace {
 
 constexpr int64_t kNoAllocMaxN = FR_MLP_NOALLOC_MAX_N;
 constexpr int64_t kMaxParams = (int64_t)H * kMaxIn + H + H * H + H + H + 1;
-constexpr int64_t kAlignFloats = 64;  // 256 bytes between the sub-buffers
-constexpr int64_t align_floats(int64_t x) { return (x + kAlignFloats - 1) / kAlignFloats * kAlignFloats; }
-constexpr int64_t scratch_floats(int64_t n, int64_t fp, int64_t np) {
-  return align_floats(n * fp) + 4 * align_floats(n * H) + 2 * align_floats(n) +
-         align_floats(((n + kSplit - 1) / kSplit) * (np + 1));
-}
-constexpr int64_t kScratchFloats = scratch_floats(kNoAllocMaxN, kMaxIn, kMaxParams);  // 14.2 MiB
+constexpr int64_t kScratchFloats = train_parts(kNoAllocMaxN) * (kMaxParams + 1);  // 12.3 MiB
 
 }  // namespace
 
@@ -722,28 +756,12 @@ int fr_mlp_train_step_noalloc(fr_mlp_t m, const float *X, int64_t n, int64_t ldx
   if (n <= 0 || n > kNoAllocMaxN)
     return fr_fail(FR_ERR_ARG, "n must be in 1.." + std::to_string(kNoAllocMaxN) + " for the no-allocation step");
   const Net &net = m->net;
-  if (scratch_floats(n, net.FP, net.np) > kScratchFloats) return fr_fail(FR_ERR_ARG, "batch exceeds the scratch array");
+  if (train_parts(n) * (net.np + 1) > kScratchFloats) return fr_fail(FR_ERR_ARG, "batch exceeds the scratch array");
   float *base = nullptr;
   int rc = scratch_address(m->device, &base);
   if (rc) return rc;
-  // every entry of these buffers that a kernel reads is first written by this call's kernels
-  // (activations and deltas for samples < n, every partial sum of every split)
-  TrainBufs tb;
-  float *q = base;
-  auto take = [&](int64_t nf) {
-    float *r = q;
-    q += align_floats(nf);
-    return r;
-  };
-  tb.xh = take(n * net.FP);
-  tb.h1 = take(n * H);
-  tb.h2 = take(n * H);
-  tb.d1 = take(n * H);
-  tb.d2 = take(n * H);
-  tb.dz = take(n);
-  tb.sq = take(n);
-  tb.part = take(((n + kSplit - 1) / kSplit) * (net.np + 1));
-  return grad_pass(m, X, n, ldx, t, true, lr, loss, &tb);
+  // (every entry of the partial gradients that the Adam kernel reads is first written by this call)
+  return grad_pass(m, X, n, ldx, t, true, lr, loss, base);
 }
 
 }  // extern "C"
