@@ -233,6 +233,10 @@ struct Cfg {
 #ifndef FR_WPE_VOLUME
 #define FR_WPE_VOLUME(P, SGS, PRE) ((P) >= 2 ? 4 : 0)
 #endif
+// The LDG face kernel: 3 is what its LDS allows up to p = 5 (2 above).
+#ifndef FR_WPE_LDG
+#define FR_WPE_LDG(P) ((P) <= 5 ? 3 : 2)
+#endif
 #ifndef FR_WPE_VOLUME32
 #define FR_WPE_VOLUME32(P) ((P) == 5 || (P) == 7 ? 4 : 0)
 #endif

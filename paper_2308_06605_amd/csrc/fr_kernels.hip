@@ -165,11 +165,11 @@ __device__ __forceinline__ void wall_face(const real *srcL, const real *fg, int 
   }
 }
 
-template <int P, typename real, bool VISC, bool SGS, bool LDG, int FBS>
+template <int P, typename real, bool VISC, bool SGS, int FBS>
 __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const real *__restrict__ face, const real *__restrict__ fgeo,
                                               const FaceRec *__restrict__ ftab, int64_t F, Phys<real> ph,
                                               int flux, real *__restrict__ fout, const double *__restrict__ nut,
-                                              real kt, real tau, real tw_gm1) {
+                                              real kt, real tw_gm1) {
   constexpr int N = P + 1, NFP = N * N;
   const int64_t gid = (int64_t)blockIdx.x * FBS + threadIdx.x;
   const int64_t fc = gid / NFP;
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const 
   const int kk = (int)(gid - fc * NFP);
   const FaceRec r = ftab[fc];
   const int fL = r.code & 7, fR = (r.code >> 3) & 7;
-  if (!LDG && (r.code & kFaceWall)) {
+  if (r.code & kFaceWall) {
     wall_face<real, VISC, SGS>(face + (((int64_t)r.eL * 6 + fL) * 20) * NFP + kk, fgeo + (fc * 4) * NFP + kk, NFP,
                                r.eL, ph, flux, nut, kt, tw_gm1, fout + (fc * 10) * NFP + kk);
     return;
@@ -202,26 +202,7 @@ __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const 
 #pragma unroll
   for (int v = 0; v < 5; ++v) UC[v] = real(0.5) * (UL[v] + UR[v]);
   real Fvn[5] = {0, 0, 0, 0, 0};
-  if (VISC && LDG) {
-    // LDG: the owner's viscous flux with its corrected gradient (the gradient slots of the face
-    // buffer hold it), plus the penalty on the jump
-    real QL[3][5];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int v = 0; v < 5; ++v) QL[i][v] = srcL[(5 + i * 5 + v) * NFP];
-    real Fv[3][5];
-    real mu = ph.mu, kap = ph.kappa;
-    if (SGS) {
-      const real mut = UL[0] * real(0.5 * (nut[r.eL] + nut[r.eR]));
-      mu += mut;
-      kap += mut * kt;
-    }
-    visc_flux_mk(UL, QL, ph.gm1, mu, kap, Fv);
-#pragma unroll
-    for (int v = 0; v < 5; ++v)
-      Fvn[v] = Fv[0][v] * nh[0] + Fv[1][v] * nh[1] + Fv[2][v] * nh[2] + tau * (UR[v] - UL[v]);
-  } else if (VISC) {
+  if (VISC) {
     // BR2: mean of the broken gradients plus the two face liftings, which combine to
     // sigma N (U_R - U_L) with N the owner's normal
     const real sig = fg[3 * NFP];
@@ -250,8 +231,7 @@ __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const 
   real *dst = fout + (fc * 10) * NFP + kk;
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
-    // U^ - U_L: the mean (BR2) or the non-owner's trace (LDG)
-    face_store<NFP>(LDG ? UR[v] - UL[v] : real(0.5) * (UR[v] - UL[v]), &dst[v * NFP]);
+    face_store<NFP>(real(0.5) * (UR[v] - UL[v]), &dst[v * NFP]);  // U^C - U_L
     face_store<NFP>(nm * (Fi[v] - Fvn[v]), &dst[(5 + v) * NFP]);
   }
 }
@@ -620,101 +600,165 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
 }
 
 // ------------------------------------------------------------------------------------------
-// LDG: each element's corrected gradient (section "FR Algorithm", the viscous flux by the local
-// DG method). The common solution is the face non-owner's trace, so U^ - U_K = U_R - U_L on
-// the faces the element owns and 0 on the others. The corrected physical gradient is
-// interpolated to the element's face points, into the gradient slots of its own face-buffer
-// entries; the face kernel reads the owner's. Runs after a pre-pass that wrote U_f only.
+// K2 of the local DG viscous flux (section "FR Algorithm"): per element, the common flux of the
+// faces it owns. The common solution is the face non-owner's trace, so U^ - U_K = U_R - U_L on the
+// faces the element owns and 0 on the others, and the common viscous flux is the owner's,
+// F_v(U_L, q_L) . n plus tau times the jump: both need the neighbours' traces U_R (the pre-pass
+// wrote them) and nothing else of theirs. So the corrected gradient q stays in LDS: only its traces
+// on owned faces are formed, and used at once. Writes U_R - U_L and the owner's transformed
+// common flux, as k_face does. 20^3 p=4 (us): a kernel
+// that wrote the traces of q on every face, 120.8, and the face kernel that read the owner's, 36.7
+// -> 67.6, 3.1 TB/s of the bytes needed; what holds it is the 12 waves per CU its LDS allows.
 // ------------------------------------------------------------------------------------------
 template <int P>
-__global__ __launch_bounds__(Cfg<P>::BLOCK) void k_ldg_grad(const double *__restrict__ X,
-                                                             const double *__restrict__ geo,
-                                                             const FaceRef *__restrict__ fref,
-                                                             const FaceRec *__restrict__ ftab,
-                                                             double *__restrict__ face, int64_t E,
-                                                             OpsT<double> ops) {
+constexpr int kLdgElems = Cfg<P>::EPB > 1 ? Cfg<P>::EPB / 2 : 1;  // small blocks: 20 N_s + 5 N_f doubles of LDS each
+template <int P, bool SGS>
+__global__ __launch_bounds__(kLdgElems<P> * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_LDG(P)) void k_ldg_face(
+    const double *__restrict__ X, const double *__restrict__ geo, const FaceRef *__restrict__ fref,
+    const FaceRec *__restrict__ ftab, const double *__restrict__ face, const double *__restrict__ fgeo, int64_t E,
+    OpsT<double> ops, Phys<double> ph, int flux, double *__restrict__ fout, const double *__restrict__ nut, double kt,
+    double tau) {
   using C = Cfg<P>;
-  constexpr int N = C::N, NS = C::NS, NFP = C::NFP, NF = C::NF, EPB = C::EPB;
-  __shared__ double sU[EPB][5][NS];
-  __shared__ double sJ[EPB][5][NF];
-  __shared__ double sG[EPB][15][NS];
+  constexpr int N = C::N, NS = C::NS, NFP = C::NFP, NF = C::NF, EPB = kLdgElems<P>;
+  __shared__ double sAll[EPB][20 * NS + 5 * NF];  // U, then q [i][v]; U_R - U_L, 0 on faces it does not own [v]
+  constexpr int NOP = N * N + 2 * N;
+  __shared__ double sOp[NOP + 2 * N];  // D, gcL, gcR; then l(-1), l(+1)
+  for (int i = threadIdx.x; i < NOP + 2 * N; i += EPB * NS)
+    sOp[i] = i < NOP ? op_entry<N>(ops, i) : (i < NOP + N ? ops.lm[i - NOP] : ops.lp[i - NOP - N]);
   const int slot = threadIdx.x / NS, t = threadIdx.x - slot * NS;
   const int64_t e = (int64_t)blockIdx.x * EPB + slot;
   const bool act = e < E;
   const int idx[3] = {t % N, (t / N) % N, t / (N * N)};
+  double *sU = sAll[slot], *sG = sU + 5 * NS, *sJ = sU + 20 * NS;
   double ja[9], iJ = 0;
+  unsigned own = 0;  // the faces this element owns
   if (act) {
 #pragma unroll
-    for (int v = 0; v < 5; ++v) sU[slot][v][t] = X[(e * 5 + v) * NS + t];
+    for (int f = 0; f < 6; ++f) own |= ((unsigned)(fref[e * 6 + f].code >> 6) & 1u) << f;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) sU[v * NS + t] = X[(e * 5 + v) * NS + t];
 #pragma unroll
     for (int c = 0; c < 9; ++c) ja[c] = geo[(e * 10 + c) * NS + t];
     iJ = geo[(e * 10 + 9) * NS + t];
-    for (int fp = t; fp < NF; fp += NS) {
-      const int f = fp / NFP, kk = fp - f * NFP;
-      const FaceRef fr = fref[e * 6 + f];
-      if ((fr.code >> 6) & 1) {
-        const FaceRec r = ftab[fr.fid];
-        const int fR = (r.code >> 3) & 7;
-        const bool swp = (r.code >> 6) & 1, flu = (r.code >> 7) & 1, flv = (r.code >> 8) & 1;
-        const int a = kk % N, b = kk / N;
-        const int uu = swp ? b : a, vv = swp ? a : b;
-        const int kr = (flu ? P - uu : uu) + N * (flv ? P - vv : vv);
-        const double *own = face + ((e * 6 + f) * 20) * NFP + kk;
-        const double *nbr = face + (((int64_t)r.eR * 6 + fR) * 20) * NFP + kr;
-#pragma unroll
-        for (int v = 0; v < 5; ++v) sJ[slot][v][fp] = nbr[v * NFP] - own[v * NFP];
-      } else {
-#pragma unroll
-        for (int v = 0; v < 5; ++v) sJ[slot][v][fp] = 0.0;
-      }
-    }
   }
-  __syncthreads();
+  const int npts = __popc(own) * NFP;
+  // owned face point q: its face, the line through it and the neighbour's values there
+  struct Point {
+    int f, kk, b0, stride;
+    FaceRec rec;
+    int64_t fid;
+    const double *nbr;
+  };
+  auto point = [&](int q) {
+    Point pt;
+    unsigned m = own;
+    for (int j = q / NFP; j > 0; --j) m &= m - 1;
+    pt.f = __ffs(m) - 1;
+    pt.kk = q % NFP;
+    const int a = pt.kk % N, b = pt.kk / N, d = pt.f >> 1;
+    pt.stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+    pt.b0 = d == 0 ? N * pt.kk : (d == 1 ? a + N * N * b : pt.kk);
+    pt.fid = fref[e * 6 + pt.f].fid;
+    pt.rec = ftab[pt.fid];
+    const int fR = (pt.rec.code >> 3) & 7;
+    const bool swp = (pt.rec.code >> 6) & 1, flu = (pt.rec.code >> 7) & 1, flv = (pt.rec.code >> 8) & 1;
+    const int uu = swp ? b : a, vv = swp ? a : b;
+    const int kr = (flu ? P - uu : uu) + N * (flv ? P - vv : vv);
+    pt.nbr = face + (((int64_t)pt.rec.eR * 6 + fR) * 20) * NFP + kr;
+    return pt;
+  };
+  auto trace = [&](const double *src, const Point &pt, const double *ell) {
+    double acc = 0;
+#pragma unroll
+    for (int c = 0; c < N; ++c) acc = fma(ell[c], src[pt.b0 + c * pt.stride], acc);
+    return acc;
+  };
+  if (act) {
+    // the faces the element does not own have no jump
+    for (int q = t; q < NF; q += NS)
+      if (!((own >> (q / NFP)) & 1u)) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) sJ[v * NF + q] = 0.0;
+      }
+  }
+  __syncthreads();  // sOp is the block's
+  for (int q = t; q < npts; q += NS) {
+    const Point pt = point(q);
+    double UR[5], ell[N];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) UR[v] = pt.nbr[v * NFP];
+#pragma unroll
+    for (int c = 0; c < N; ++c) ell[c] = sOp[NOP + (pt.f & 1) * N + c];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) sJ[v * NF + pt.f * NFP + pt.kk] = UR[v] - trace(sU + v * NS, pt, ell);
+  }
+  elem_sync<NS>();
   if (act) {
     double dU[3][5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      double d0 = 0, d1 = 0, d2 = 0;
-#pragma unroll
-      for (int c = 0; c < N; ++c) {
-        d0 += ops.D[idx[0] * N + c] * sU[slot][v][c + N * (idx[1] + N * idx[2])];
-        d1 += ops.D[idx[1] * N + c] * sU[slot][v][idx[0] + N * (c + N * idx[2])];
-        d2 += ops.D[idx[2] * N + c] * sU[slot][v][idx[0] + N * (idx[1] + N * c)];
-      }
-      dU[0][v] = d0;
-      dU[1][v] = d1;
-      dU[2][v] = d2;
-    }
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const int u = d == 0 ? 1 : 0, w = d == 2 ? 1 : 2;
       const int kk = idx[u] + N * idx[w];
-      const double cL = ops.gcL[idx[d]], cR = ops.gcR[idx[d]];
+      const int stride = d == 0 ? 1 : (d == 1 ? N : N * N);
+      const int b0 = t - idx[d] * stride;
+      const double cL = sOp[N * N + idx[d]], cR = sOp[N * N + N + idx[d]];
+      double row[N];
 #pragma unroll
-      for (int v = 0; v < 5; ++v)
-        dU[d][v] += sJ[slot][v][(2 * d) * NFP + kk] * cL + sJ[slot][v][(2 * d + 1) * NFP + kk] * cR;
+      for (int c = 0; c < N; ++c) row[c] = sOp[idx[d] * N + c];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        double acc = 0;
+#pragma unroll
+        for (int c = 0; c < N; ++c) acc = fma(row[c], sU[v * NS + b0 + c * stride], acc);
+        dU[d][v] = acc + fma(sJ[v * NF + (2 * d) * NFP + kk], cL, sJ[v * NF + (2 * d + 1) * NFP + kk] * cR);
+      }
     }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int v = 0; v < 5; ++v)
-        sG[slot][i * 5 + v][t] = iJ * (ja[i] * dU[0][v] + ja[3 + i] * dU[1][v] + ja[6 + i] * dU[2][v]);
+        sG[(i * 5 + v) * NS + t] = iJ * dot3(ja[i], dU[0][v], ja[3 + i], dU[1][v], ja[6 + i], dU[2][v]);
   }
-  __syncthreads();
-  if (!act) return;
-  // items (gradient component i, face point): 5 values each
-  for (int q = t; q < 3 * NF; q += NS) {
-    const int i = q / NF, fp = q - i * NF;
-    const int f = fp / NFP, kk = fp - f * NFP;
-    const int a = kk % N, b = kk / N, d = f >> 1;
-    const double *ell = (f & 1) ? ops.lp : ops.lm;
-    double *dst = face + ((e * 6 + f) * 20 + 5 + 5 * i) * NFP + kk;
+  elem_sync<NS>();
+  for (int q = t; q < npts; q += NS) {
+    const Point pt = point(q);
+    double UL[5], UR[5], QL[3][5], ell[N];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) UR[v] = pt.nbr[v * NFP];
+    const double *fg = fgeo + (pt.fid * 4) * NFP + pt.kk;
+    const double NL[3] = {fg[0], fg[NFP], fg[2 * NFP]};
+#pragma unroll
+    for (int c = 0; c < N; ++c) ell[c] = sOp[NOP + (pt.f & 1) * N + c];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) UL[v] = trace(sU + v * NS, pt, ell);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) QL[i][v] = trace(sG + (i * 5 + v) * NS, pt, ell);
+      // the sums are done here: otherwise every LDS read is issued first, and spilled
+      asm volatile("" : "+v"(QL[i][0]), "+v"(QL[i][1]), "+v"(QL[i][2]), "+v"(QL[i][3]), "+v"(QL[i][4])::"memory");
+    }
+    const double nm = sqrt(NL[0] * NL[0] + NL[1] * NL[1] + NL[2] * NL[2]);
+    const double inm = 1.0 / nm;
+    const double nh[3] = {NL[0] * inm, NL[1] * inm, NL[2] * inm};
+    double mu = ph.mu, kap = ph.kappa;
+    if (SGS) {
+      const double mut = UL[0] * (0.5 * (nut[pt.rec.eL] + nut[pt.rec.eR]));
+      mu += mut;
+      kap += mut * kt;
+    }
+    double Fv[3][5], Fvn[5], Fi[5];
+    visc_flux_mk(UL, QL, ph.gm1, mu, kap, Fv);
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+      Fvn[v] = Fv[0][v] * nh[0] + Fv[1][v] * nh[1] + Fv[2][v] * nh[2] + tau * (UR[v] - UL[v]);
+    if (flux == 0) rusanov(UL, UR, nh, ph, Fi);
+    else roe(UL, UR, nh, ph, Fi);
+    double *dst = fout + (pt.fid * 10) * NFP + pt.kk;
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      double acc = 0;
-#pragma unroll
-      for (int c = 0; c < N; ++c) acc += ell[c] * sG[slot][i * 5 + v][line_pt<N>(d, c, a, b)];
-      face_store<NFP>(acc, &dst[v * NFP]);
+      face_store<NFP>(UR[v] - UL[v], &dst[v * NFP]);
+      face_store<NFP>(nm * (Fi[v] - Fvn[v]), &dst[(5 + v) * NFP]);
     }
   }
 }
@@ -994,18 +1038,17 @@ static int launch_stage_t(DeviceMesh &dm, const double *X, StageArgs st, double 
                        X, (const real *)dm.geo, (real *)dm.face, dm.E, ops);
     HIPCHK(hipGetLastError());
   }
-  if (LDG) {
-    static_assert(sizeof(OpsT<double>) == sizeof(Ops1D), "operator tables share one layout");
-    OpsT<double> od;
-    std::memcpy(&od, &dm.ops, sizeof od);
-    hipLaunchKernelGGL((k_ldg_grad<P>), dim3((unsigned)((dm.E + C::EPB - 1) / C::EPB)), dim3(C::BLOCK), 0, s, X,
-                       (const double *)dm.geo, dm.fref, dm.ftab, (double *)dm.face, dm.E, od);
-    HIPCHK(hipGetLastError());
-  }
   if (ms) HIPCHK(hipEventRecord(ev[1], s));
-  hipLaunchKernelGGL((k_face<P, real, VISC, SGS, LDG, FBS>), dim3((unsigned)fblocks), dim3(FBS), 0, s,
-                     (const real *)dm.face, (const real *)dm.fgeo, dm.ftab, dm.F, ph, dm.flux, (real *)dm.fout,
-                     dm.nut, kt, real(dm.ldg_tau), real(dm.wall_T / (dm.phys.gamma - 1.0)));
+  if constexpr (LDG) {
+    constexpr int EL = kLdgElems<P>;
+    hipLaunchKernelGGL((k_ldg_face<P, SGS>), dim3((unsigned)((dm.E + EL - 1) / EL)), dim3(EL * C::NS), 0, s, X,
+                       (const double *)dm.geo, dm.fref, dm.ftab, (const double *)dm.face, (const double *)dm.fgeo,
+                       dm.E, ops, ph, dm.flux, (double *)dm.fout, dm.nut, kt, dm.ldg_tau);
+  } else {
+    hipLaunchKernelGGL((k_face<P, real, VISC, SGS, FBS>), dim3((unsigned)fblocks), dim3(FBS), 0, s,
+                       (const real *)dm.face, (const real *)dm.fgeo, dm.ftab, dm.F, ph, dm.flux, (real *)dm.fout,
+                       dm.nut, kt, real(dm.wall_T / (dm.phys.gamma - 1.0)));
+  }
   HIPCHK(hipGetLastError());
   if (ms) HIPCHK(hipEventRecord(ev[2], s));
   if (st.pre_next) {
