@@ -222,8 +222,11 @@ struct Cfg {
 // p = 2 on the FP64 volume kernels ask for 4 (at most 128 VGPRs): left alone the compiler takes
 // up to 165 (3 waves; 2 for some) to hoist LDS reads, and the kernels are short of waves, not of
 // loads in flight. They fit without spills, but for 12 bytes per lane at p = 3 and 20 to 28 at
-// p = 6 in the instances without the fused pre-pass. The FP32 form's volume kernel asks for 4
-// at p = 5 and p = 7 and takes about 100 VGPRs at every degree.
+// p = 6 in the instances without the fused pre-pass. The FP32 form's volume kernel with the
+// fused pre-pass fits 96 VGPRs, 5 waves, at p = 2..6 (13x11x17 p=5 channel: 56.3 -> 52.1 us; 2431
+// blocks then take two rounds of the chip instead of three). Without it 96 spill (36 -> 48 us
+// there), so it asks for 4 at p = 5 and the compiler's choice is 4 elsewhere; at p = 7 a block is
+// eight waves and a fifth wave per SIMD does not fit another.
 #ifndef FR_WPE_PREPASS
 #define FR_WPE_PREPASS(P) 0
 #endif
@@ -238,7 +241,7 @@ struct Cfg {
 #define FR_WPE_LDG(P) ((P) <= 5 ? 3 : 2)
 #endif
 #ifndef FR_WPE_VOLUME32
-#define FR_WPE_VOLUME32(P) ((P) == 5 || (P) == 7 ? 4 : 0)
+#define FR_WPE_VOLUME32(P, PRE) ((P) == 7 || ((P) == 5 && !(PRE)) ? 4 : ((P) >= 2 && (PRE) ? 5 : 0))
 #endif
 #define FR_WPE_ATTR(w) __attribute__((amdgpu_waves_per_eu((w) > 0 ? (w) : 1, (w) > 0 ? 8 : 8)))
 

@@ -436,16 +436,28 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
   double *sM = sMall[slot];
   double *sJm = sJmall[slot];
   const int64_t base = e * 5 * NS + t;
-  double Xd[5], jad[9], iJd = 0, r1[5], r2[5];
+  // the metric terms in FP32 and the transformed mass flux per direction, formed from the FP64 ones
+  // at once: their 18 registers are not live across the gradient phase
+  float ja[9];
+  double Xd[5], iJd = 0, Fm[3], r1[5], r2[5];
   if (act) {
+    double jad[9];
+    FaceRef frf[R];  // loaded first: the loads of the faces' data depend on them
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (t + r * NS < NF) frf[r] = fref[e * 6 + (t + r * NS) / NFP];
 #pragma unroll
     for (int v = 0; v < 5; ++v) Xd[v] = X[base + v * NS];
 #pragma unroll
     for (int c = 0; c < 9; ++c) jad[c] = geo[(e * 10 + c) * NS + t];
     iJd = geo[(e * 10 + 9) * NS + t];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) ja[c] = float(jad[c]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) Fm[d] = dot3(jad[d * 3 + 0], Xd[1], jad[d * 3 + 1], Xd[2], jad[d * 3 + 2], Xd[3]);
     if (MST) {
 #pragma unroll
-      for (int c = 0; c < 9; ++c) sMetall[slot][c * NS + t] = float(jad[c]);
+      for (int c = 0; c < 9; ++c) sMetall[slot][c * NS + t] = ja[c];
       sMetall[slot][9 * NS + t] = float(iJd);
     }
 #pragma unroll
@@ -453,7 +465,7 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
       const int fp = t + r * NS;
       if (fp < NF) {
         const int f = fp / NFP, kk = fp - f * NFP;
-        const FaceRef fr = fref[e * 6 + f];
+        const FaceRef fr = frf[r];
         const int a = kk % N, b = kk / N;
         const bool swp = (fr.code >> 3) & 1, flu = (fr.code >> 4) & 1, flv = (fr.code >> 5) & 1;
         const int uu = swp ? b : a, vv = swp ? a : b;
@@ -480,15 +492,11 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
   if (OPL || WPF) __syncthreads();  // the tables are the block's
   else elem_sync<NS>();
   float F[3][5];  // [direction][component]: 0 unused, 1-3 momentum, 4 reduced energy
-  double Fm[3];   // transformed mass flux per direction (FP64)
   if (act) {
     float Up[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) Up[v] = sU[v * NS + t];
     if (VISC) {
-      float ja[9];
-#pragma unroll
-      for (int c = 0; c < 9; ++c) ja[c] = float(jad[c]);
       const float iJ = float(iJd);
       float dU[3][5];
 #pragma unroll
@@ -537,13 +545,9 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
       const float f0 = F[0][v], f1 = F[1][v], f2 = F[2][v];
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        float f = dot3(float(jad[d * 3 + 0]), f0, float(jad[d * 3 + 1]), f1, float(jad[d * 3 + 2]), f2);
+        float f = dot3(ja[d * 3 + 0], f0, ja[d * 3 + 1], f1, ja[d * 3 + 2], f2);
         F[d][v] = f;
       }
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      Fm[d] = dot3(jad[d * 3 + 0], Xd[1], jad[d * 3 + 1], Xd[2], jad[d * 3 + 2], Xd[3]);
     }
     // (assigned per mode, not initialised up front: a live range from the kernel's start
     // costs the gradient phase its registers)
@@ -741,7 +745,7 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
 }
 
 template <int P, bool VISC, int EPBX, bool PRE>
-__global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME32(P)) void k_volume32(
+__global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME32(P, PRE)) void k_volume32(
     const double *X, const double *__restrict__ geo, const FaceRef *__restrict__ fref,
     const float *__restrict__ fout32, const double *__restrict__ foutm, int64_t E, OpsT<float> ops,
     OpsT<double> opsd, Phys<float> ph, Ref32 ref, StageArgs st, double *out0,
@@ -860,7 +864,7 @@ __global__ __launch_bounds__(FBS) void k_face32_multi(const Slice32 *__restrict_
 }
 
 template <int P, bool VISC, int EPBX, bool PRE>
-__global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME32(P)) void k_volume32_multi(
+__global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME32(P, PRE)) void k_volume32_multi(
     const Slice32 *__restrict__ tab, const int64_t *__restrict__ first, int nm, int s, OpsT<float> ops,
     OpsT<double> opsd) {
   const int m = slice_of(first, nm, blockIdx.x);
