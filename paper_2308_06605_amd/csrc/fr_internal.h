@@ -154,6 +154,7 @@ struct DeviceMesh {
   int64_t n_ghost = 0;    // face slots after the 6E local ones in face / face32 / facem: the
                           // other parts' faces of a partition group, filled by the halo unpack
   int *flag = nullptr;    // non-finite flag
+  double *kin = nullptr;  // kinetic-energy sums: the three totals, then the blocks' partial sums
   bool check_finite = false;
   void *stream = nullptr;
   int64_t bytes = 0;

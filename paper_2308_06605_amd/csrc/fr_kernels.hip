@@ -38,6 +38,10 @@
 
 using namespace frk;
 
+struct Weights1D {
+  double w[kMaxN];
+};
+
 // ------------------------------------------------------------------------------------------
 // K1: element pre-pass
 // ------------------------------------------------------------------------------------------
@@ -315,6 +319,10 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
   const int64_t base = e * 5 * NS + t;
   if (act) {
     if (OPX && t < NOP) opv = op_entry<N>(ops, t);
+    FaceRef frf[R];  // loaded first: the loads of the faces' data depend on them
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (t + r * NS < NF) frf[r] = fref[e * 6 + (t + r * NS) / NFP];
 #pragma unroll
     for (int v = 0; v < 5; ++v) Xd[v] = X[base + v * NS];
 #pragma unroll
@@ -327,7 +335,7 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
       const int fp = t + r * NS;
       if (fp < NF) {
         const int f = fp / NFP, kk = fp - f * NFP;
-        const FaceRef fr = fref[e * 6 + f];
+        const FaceRef fr = frf[r];
         const int a = kk % N, b = kk / N;
         const bool swp = (fr.code >> 3) & 1, flu = (fr.code >> 4) & 1, flv = (fr.code >> 5) & 1;
         const int uu = swp ? b : a, vv = swp ? a : b;
@@ -768,7 +776,26 @@ __global__ __launch_bounds__(kLdgElems<P> * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_LDG(P
 // velocity polynomial u = m/rho (tensor projection on orthonormal Legendre modes, one
 // direction at a time through LDS) and five volume-averaged invariants of its broken gradient
 // (a fixed-order tree reduction over the element's points). FP64, rounded to float once.
+//
+// Bound by the instructions issued: FP64 logarithms and divisions, and pow. The invariants of all of
+// a block's elements are therefore finished by one wave, a lane per element and invariant, with one
+// logarithm and two divisions for the five (each element's first lane did them all, one after the
+// other, with the other lanes of its wave idle). 16^3 p=3 (us): 16.4 -> 10.7.
 // ------------------------------------------------------------------------------------------
+// x + (x of lane t + H), for the lanes t < H of a tree over a wave: the DPP row shifts within 16
+// lanes, a lane permutation above.
+template <int H>
+__device__ __forceinline__ double wave_tree_add(double x) {
+  if constexpr (H >= 16) {
+    return x + __shfl_down(x, H);
+  } else {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, 0x100 | H, 0xf, 0xf, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), 0x100 | H, 0xf, 0xf, false);
+    return x + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+  }
+}
+
 template <int P>
 __global__ __launch_bounds__(Cfg<P>::BLOCK) void k_sgs_features(const double *__restrict__ X,
                                                                  const double *__restrict__ geo, int64_t E,
@@ -778,9 +805,14 @@ __global__ __launch_bounds__(Cfg<P>::BLOCK) void k_sgs_features(const double *__
   constexpr int N = C::N, NS = C::NS, EPB = C::EPB, NFT = NS + 4;
   constexpr int P2 = NS <= 1 ? 1 : (NS <= 2 ? 2 : (NS <= 4 ? 4 : (NS <= 8 ? 8 : (NS <= 16 ? 16 : (NS <= 32 ? 32 :
                      (NS <= 64 ? 64 : (NS <= 128 ? 128 : (NS <= 256 ? 256 : 512))))))));
+  constexpr bool WAVE = NS == 64;  // an element is a wave: its sums by lane exchange, without LDS
   __shared__ double sA[EPB][3][NS];
   __shared__ double sB[EPB][3][NS];
-  __shared__ double sR[EPB][6][NS];
+  __shared__ double sR[WAVE ? 1 : EPB][WAVE ? 1 : 6][WAVE ? 1 : NS];
+  __shared__ double sS[EPB][6];       // the elements' sums
+  __shared__ double sOp[2 * N * N];   // D, then the modal projection
+  for (int i = threadIdx.x; i < 2 * N * N; i += EPB * NS) sOp[i] = i < N * N ? ops.D[i] : so.Lm[i - N * N];
+  const double *D = sOp, *Lm = sOp + N * N;
   const int slot = threadIdx.x / NS, t = threadIdx.x - slot * NS;
   const int64_t e = (int64_t)blockIdx.x * EPB + slot;
   const bool act = e < E;
@@ -803,9 +835,9 @@ __global__ __launch_bounds__(Cfg<P>::BLOCK) void k_sgs_features(const double *__
       double d0 = 0, d1 = 0, d2 = 0;
 #pragma unroll
       for (int c = 0; c < N; ++c) {
-        d0 += ops.D[idx[0] * N + c] * sA[slot][j][c + N * (idx[1] + N * idx[2])];
-        d1 += ops.D[idx[1] * N + c] * sA[slot][j][idx[0] + N * (c + N * idx[2])];
-        d2 += ops.D[idx[2] * N + c] * sA[slot][j][idx[0] + N * (idx[1] + N * c)];
+        d0 += D[idx[0] * N + c] * sA[slot][j][c + N * (idx[1] + N * idx[2])];
+        d1 += D[idx[1] * N + c] * sA[slot][j][idx[0] + N * (c + N * idx[2])];
+        d2 += D[idx[2] * N + c] * sA[slot][j][idx[0] + N * (idx[1] + N * c)];
       }
       du[0][j] = d0;
       du[1][j] = d1;
@@ -839,68 +871,98 @@ __global__ __launch_bounds__(Cfg<P>::BLOCK) void k_sgs_features(const double *__
     for (int j = 0; j < 3; ++j) {
       double acc = 0;
 #pragma unroll
-      for (int c = 0; c < N; ++c) acc += so.Lm[idx[0] * N + c] * sA[slot][j][c + N * (idx[1] + N * idx[2])];
+      for (int c = 0; c < N; ++c) acc += Lm[idx[0] * N + c] * sA[slot][j][c + N * (idx[1] + N * idx[2])];
       sB[slot][j][t] = acc;
     }
   }
+  if constexpr (WAVE) {
 #pragma unroll
-  for (int k = 0; k < 6; ++k) sR[slot][k][t] = q[k];
-  __syncthreads();
+    for (int k = 0; k < 6; ++k) {
+      double x = q[k];
+      x = wave_tree_add<32>(x);
+      x = wave_tree_add<16>(x);
+      x = wave_tree_add<8>(x);
+      x = wave_tree_add<4>(x);
+      x = wave_tree_add<2>(x);
+      x = wave_tree_add<1>(x);
+      if (t == 0) sS[slot][k] = x;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) sR[WAVE ? 0 : slot][WAVE ? 0 : k][WAVE ? 0 : t] = q[k];
+  }
+  elem_sync<NS>();
   if (act) {  // along eta
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       double acc = 0;
 #pragma unroll
-      for (int c = 0; c < N; ++c) acc += so.Lm[idx[1] * N + c] * sB[slot][j][idx[0] + N * (c + N * idx[2])];
+      for (int c = 0; c < N; ++c) acc += Lm[idx[1] * N + c] * sB[slot][j][idx[0] + N * (c + N * idx[2])];
       sA[slot][j][t] = acc;
     }
   }
-  __syncthreads();
+  elem_sync<NS>();
   if (act) {  // along zeta; thread t now owns mode t
     double ek = 0;
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       double acc = 0;
 #pragma unroll
-      for (int c = 0; c < N; ++c) acc += so.Lm[idx[2] * N + c] * sA[slot][j][idx[0] + N * (idx[1] + N * c)];
+      for (int c = 0; c < N; ++c) acc += Lm[idx[2] * N + c] * sA[slot][j][idx[0] + N * (idx[1] + N * c)];
       ek += acc * acc;
     }
     if (t > 0) feat[e * NFT + t - 1] = (float)log(ek / 16 + 1e-12);
   }
+  if constexpr (!WAVE) {
 #pragma unroll
-  for (int h = P2 / 2; h > 0; h >>= 1) {
-    if (t < h && t + h < NS) {
+    for (int h = P2 / 2; h > 0; h >>= 1) {
+      if (t < h && t + h < NS) {
 #pragma unroll
-      for (int k = 0; k < 6; ++k) sR[slot][k][t] += sR[slot][k][t + h];
+        for (int k = 0; k < 6; ++k) sR[slot][k][t] += sR[slot][k][t + h];
+      }
+      __syncthreads();
     }
-    __syncthreads();
+    if (t == 0) {
+#pragma unroll
+      for (int k = 0; k < 6; ++k) sS[slot][k] = sR[slot][k][0];
+    }
   }
-  if (act && t == 0) {
-    const double vol = sR[slot][0][0];
-    const double s2 = sR[slot][1][0] / vol, w2 = sR[slot][2][0] / vol, r = sR[slot][3][0] / vol;
-    const double th = sR[slot][4][0] / vol, th2 = sR[slot][5][0] / vol;
-    const double eps = 1e-12;
-    float *o = feat + e * NFT + NS - 1;
-    o[0] = (float)(0.5 * log(s2 + eps));
-    o[1] = (float)(0.5 * log(w2 + eps));
-    o[2] = (float)(r / pow(s2 + eps, 1.5));
-    o[3] = (float)(th / sqrt(s2 + eps));
-    o[4] = (float)(th2 / (s2 + eps));
+  __syncthreads();
+  // item k < 5 of element es: invariant k + 1 over the volume (k = 0: s2, 1: w2, 2: r, 3: th, 4: th2)
+  for (int i = threadIdx.x; i < EPB * 5; i += EPB * NS) {
+    const int es = i / 5, k = i - 5 * es;
+    const int64_t ee = (int64_t)blockIdx.x * EPB + es;
+    if (ee < E) {
+      const double vol = sS[es][0], eps = 1e-12;
+      const double x = sS[es][k + 1] / vol;
+      float out;
+      if (k < 2) {
+        out = (float)(0.5 * log(x + eps));
+      } else {
+        const double s2e = sS[es][1] / vol + eps;
+        const double den = k == 2 ? pow(s2e, 1.5) : (k == 3 ? sqrt(s2e) : s2e);
+        out = (float)(x / den);
+      }
+      feat[ee * NFT + NS - 1 + k] = out;
+    }
   }
 }
 
 // Per-block partial sums of w|J| (1), w|J| |m|^2/(2 rho) (2) and w|J| (u.R_m - |u|^2 R_rho/2)
-// (3); one block per 256 solution points, fixed reduction order.
+// (3); one block per 256 solution points, fixed reduction order. k_kinetic_sum adds the blocks'.
 __global__ __launch_bounds__(256) void k_kinetic(const double *__restrict__ U, const double *__restrict__ R,
                                                  const double *__restrict__ geo, int64_t E, int Ns, int n,
-                                                 const double *__restrict__ w1d, double *__restrict__ part) {
+                                                 Weights1D w1d, double *__restrict__ part) {
   __shared__ double s[3][256];
+  __shared__ double w[kMaxN];
+  if (threadIdx.x < kMaxN) w[threadIdx.x] = w1d.w[threadIdx.x];
+  __syncthreads();
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   double a = 0, b = 0, c = 0;
   if (gid < E * Ns) {
     const int64_t e = gid / Ns;
     const int t = (int)(gid - e * Ns);
-    const double wJ = w1d[t % n] * w1d[(t / n) % n] * w1d[t / (n * n)] / geo[(e * 10 + 9) * Ns + t];
+    const double wJ = w[t % n] * w[(t / n) % n] * w[t / (n * n)] / geo[(e * 10 + 9) * Ns + t];
     const double *u = U + e * 5 * Ns + t;
     const double *r = R + e * 5 * Ns + t;
     const double rho = u[0], m0 = u[Ns], m1 = u[2 * Ns], m2 = u[3 * Ns];
@@ -920,6 +982,23 @@ __global__ __launch_bounds__(256) void k_kinetic(const double *__restrict__ U, c
   }
   if (threadIdx.x == 0)
     for (int q = 0; q < 3; ++q) part[blockIdx.x * 3 + q] = s[q][0];
+}
+
+// out[q] = sum over the nblk blocks of part[b][q]: one block, each thread every 256th, then a tree.
+__global__ __launch_bounds__(256) void k_kinetic_sum(const double *__restrict__ part, int64_t nblk,
+                                                     double *__restrict__ out) {
+  __shared__ double s[3][256];
+  double a[3] = {0, 0, 0};
+  for (int64_t i = threadIdx.x; i < nblk; i += 256)
+    for (int q = 0; q < 3; ++q) a[q] += part[i * 3 + q];
+  for (int q = 0; q < 3; ++q) s[q][threadIdx.x] = a[q];
+  __syncthreads();
+  for (unsigned h = 128; h > 0; h >>= 1) {
+    if (threadIdx.x < h)
+      for (int q = 0; q < 3; ++q) s[q][threadIdx.x] += s[q][threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x < 3) out[threadIdx.x] = s[threadIdx.x][0];
 }
 
 __global__ void k_nonfinite(const double *__restrict__ R, int64_t n, int *flag) {
@@ -1415,7 +1494,7 @@ int frk::destroy_device_mesh(fr_mesh_s *m) {
   else (void)hipDeviceSynchronize();
   void *bufs[] = {dm.U,     dm.R1,    dm.R2,    dm.geo,    dm.fgeo,  dm.ftab,  dm.fref, dm.face,
                   dm.fout,  dm.geo32, dm.face32, dm.facem, dm.fout32, dm.foutm, dm.flag, dm.nut,
-                  dm.feat};
+                  dm.feat, dm.kin};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   for (int32_t *b : m->send_slots)
@@ -1508,48 +1587,33 @@ int fr_kinetic_energy(fr_mesh_t m, double *out) {
   if (!valid(m) || !out) return fail(FR_ERR_ARG, "bad handle or NULL pointer");
   if (int rc = reject_part(m, "fr_kinetic_energy")) return rc;
   DeviceMesh &dm = m->dm;
-  const size_t M = (size_t)dm.E * 5 * dm.Ns;
   const int64_t npts = dm.E * dm.Ns;
   const int64_t nblk = (npts + 255) / 256;
   hipStream_t s = (hipStream_t)dm.stream;
+  // The residual goes to the first RK register: no step keeps anything in it (every scheme's first
+  // stage writes it before any stage reads it). The partial sums are kept with the handle.
+  if (int rc = ensure_registers(dm, FR_LSRK45)) return rc;
+  if (!dm.kin) {
+    HIPCHK(hipMalloc(&dm.kin, (nblk + 1) * 3 * sizeof(double)));
+    dm.bytes += (nblk + 1) * 3 * sizeof(double);
+  }
   // Gauss-Legendre weights from the correction tables: w_a = l_a(+1) / g_R'(x_a)
-  double w[kMaxN];
-  for (int a = 0; a < dm.n; ++a) w[a] = dm.ops.lp[a] / dm.ops.gcR[a];
-  double *R = nullptr, *part = nullptr, *wd = nullptr;
-  std::vector<double> hp(nblk * 3);
-  int rc = FR_OK;
-  hipError_t e = hipMalloc(&R, M * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&part, nblk * 3 * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&wd, kMaxN * sizeof(double));
-  if (e == hipSuccess) e = hipMemcpyAsync(wd, w, kMaxN * sizeof(double), hipMemcpyHostToDevice, s);
-  if (e != hipSuccess) rc = fail(FR_ERR_HIP, std::string("kinetic energy setup: ") + hipGetErrorString(e));
-  if (rc == FR_OK) {
-    StageArgs st{};
-    st.mode = kModeResidual;
-    rc = launch_stage(dm, dm.U, st, R, nullptr, nullptr);
-  }
-  if (rc == FR_OK) {
-    hipLaunchKernelGGL(k_kinetic, dim3((unsigned)nblk), dim3(256), 0, s, dm.U, R, (const double *)dm.geo, dm.E,
-                       dm.Ns, dm.n, wd, part);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(hp.data(), part, nblk * 3 * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) rc = fail(FR_ERR_HIP, std::string("kinetic energy: ") + hipGetErrorString(e));
-  }
-  if (rc == FR_OK) {
-    double a = 0, b = 0, c = 0;
-    for (int64_t i = 0; i < nblk; ++i) {
-      a += hp[i * 3];
-      b += hp[i * 3 + 1];
-      c += hp[i * 3 + 2];
-    }
-    out[0] = b / a;
-    out[1] = c / a;
-  }
-  if (R) (void)hipFree(R);
-  if (part) (void)hipFree(part);
-  if (wd) (void)hipFree(wd);
-  return rc;
+  Weights1D w{};
+  for (int a = 0; a < dm.n; ++a) w.w[a] = dm.ops.lp[a] / dm.ops.gcR[a];
+  StageArgs st{};
+  st.mode = kModeResidual;
+  if (int rc = launch_stage(dm, dm.U, st, dm.R1, nullptr, nullptr)) return rc;
+  hipLaunchKernelGGL(k_kinetic, dim3((unsigned)nblk), dim3(256), 0, s, dm.U, dm.R1, (const double *)dm.geo, dm.E,
+                     dm.Ns, dm.n, w, dm.kin + 3);
+  HIPCHK(hipGetLastError());
+  hipLaunchKernelGGL(k_kinetic_sum, dim3(1), dim3(256), 0, s, dm.kin + 3, nblk, dm.kin);
+  HIPCHK(hipGetLastError());
+  double sum[3];
+  HIPCHK(hipMemcpyAsync(sum, dm.kin, sizeof sum, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  out[0] = sum[1] / sum[0];
+  out[1] = sum[2] / sum[0];
+  return FR_OK;
 }
 
 int fr_mesh_info(fr_mesh_t m, int64_t *n_elem, int32_t *n_sol, int64_t *device_bytes) {
