@@ -144,6 +144,8 @@ int fr_get_state(fr_mesh_t m, double *U, int on_device);
  *        leave lanes of the last wave idle (p = 5, 6), two elements;
  *   fbs  threads per block of the face kernel: 0 = 256, 1 = 128, 2 = 64 (with FR_LDG the face
  *        kernel works per element and has a block of its own).
+ * Until one is chosen (fr_get_tiles then gives 0, 0) a single mesh's stages take blocks by its size:
+ * small meshes the smaller ones.
  * Results are bitwise independent of the tiles (every thread does the same arithmetic). A batch
  * captures the tiles in force at its creation. */
 int fr_set_tiles(fr_mesh_t m, int32_t epb, int32_t fbs);

@@ -150,7 +150,8 @@ __device__ __forceinline__ double body_force(const StageArgs &st, const double X
 }
 
 // x: the state the stage was evaluated on; R: its residual; r1, r2: the registers' old values.
-//   LSRK45:   dU <- a dU + dt R; U <- x + b dU                       (out0 = U, reg1 = dU)
+//   LSRK45:   dU <- a dU + dt R; U <- x + b dU                       (out0 = U, reg1 = dU, which the
+//                                                                     last stage does not store)
 //   RK4:      acc <- acc + w R; S <- Q + c dt R, or at the last stage Q <- Q + dt acc
 //                                                (out0 = Q, reg1 = acc, reg2 = S)
 //   SSP(10,4) (out0 = q1 = U, reg1 = q2): stages 0-3 and 5-8 take a forward-Euler step
@@ -167,7 +168,7 @@ __device__ __forceinline__ double rk_store(const StageArgs &st, int64_t o, doubl
   if (st.mode == kModeLSRK) {
     const double du = fma(st.a, r1, st.dt * R);
     const double u = fma(st.b, du, x);
-    reg1[o] = du;
+    if (!st.last) reg1[o] = du;
     out0[o] = u;
     return u;
   }

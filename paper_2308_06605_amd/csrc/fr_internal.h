@@ -92,7 +92,8 @@ enum StageMode : int32_t {
 struct StageArgs {
   int32_t mode;
   int32_t first;  // RK4: first stage (acc not read); LSRK: a == 0
-  int32_t last;   // RK4: last stage (Q updated instead of S)
+  int32_t last;   // RK4: last stage (Q updated instead of S); LSRK: last stage (dU is not stored:
+                  // the next step's first stage does not read it)
   int32_t stage;  // SSP: stage index 0..9
   double a, b, dt;  // LSRK coefficients and step
   double w, cdt;    // RK4 weight and next-stage offset c_{i+1} * dt
@@ -137,6 +138,7 @@ struct DeviceMesh {
   double ref_rho = 1.0, ref_p = 0.0;
   int tile_epb = 0;             // element kernels: 0 = 256/Ns elements per block, 1 = half
   int tile_fbs = 0;             // face kernel block: 0 = 256, 1 = 128, 2 = 64 threads
+  bool tiles_set = false;       // the tiles were chosen (fr_set_tiles, fr_autotune); see tiles_of
   bool fuse = true;             // each stage's volume kernel runs the next stage's pre-pass
   bool walls = false;           // isothermal no-slip wall faces present
   double wall_T = 1.0;          // their temperature p/rho
@@ -238,6 +240,24 @@ inline int tile_elements(int Ns, int epb) {
   const int e0 = (256 / Ns) > 64 ? 64 : ((256 / Ns) > 0 ? (256 / Ns) : 1);
   if (epb == 0) return e0;
   return e0 > 1 ? e0 / 2 : (Ns % 64 != 0 && 2 * Ns <= 1024 ? 2 : 1);
+}
+// The tiles a single mesh's kernels are launched with: those chosen, or until then a choice by size.
+// Where half blocks still leave at most one per CU (256), they spread a small mesh over more of the
+// chip; face blocks of one wave do the same up to four waves per CU. Elements of 125 points (p = 4)
+// always take a block each (two waves meet at its barriers instead of four). Time per LSRK45 stage
+// (us), 256/N_s elements and 256 threads against the choice here: p=1 1000 elements 15.5 / 12.0, p=2
+// 343 15.4 / 13.6, p=3 125 14.5 / 12.3, p=4 64 15.9 / 13.7, p=4 2197 52.3 / 48.7 (FP64; FP32 form
+// 15.4 / 12.6, 15.6 / 14.1, 13.0 / 12.4, 14.4 / 13.4, 35.5 / 34.8); beyond the limits there is no
+// difference or a loss (p=2 2197 22.5 against 23.8 with half blocks). Multi-mesh groups keep
+// 256/N_s and 256.
+struct Tiles {
+  int epb, fbs;
+};
+inline Tiles tiles_of(const DeviceMesh &dm) {
+  if (dm.tiles_set) return {dm.tile_epb, dm.tile_fbs};
+  const int whole = tile_elements(dm.Ns, 0), half = tile_elements(dm.Ns, 1);
+  const bool split = half < whole && (dm.Ns == 125 || dm.E <= (int64_t)256 * half);
+  return {split ? 1 : 0, dm.F * dm.Nfp <= 65536 ? 2 : 0};
 }
 // The register update of stage s of `scheme` with step dt (st.mode, coefficients) and the state,
 // output and register arrays that stage reads and writes on the handle's buffers.

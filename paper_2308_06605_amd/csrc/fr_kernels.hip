@@ -1158,13 +1158,14 @@ template <int P, typename real, bool VISC, bool SGS, bool LDG>
 static int launch_stage_tiles(DeviceMesh &dm, const double *X, StageArgs st, double *o, double *r1, double *r2,
                               double *ms) {
   constexpr int E0 = Cfg<P>::EPB, E1 = Cfg<P>::EPB2;
-  if (dm.tile_epb == 0) {
-    if (dm.tile_fbs == 0) return launch_stage_t<P, real, VISC, SGS, LDG, E0, 256>(dm, X, st, o, r1, r2, ms);
-    if (dm.tile_fbs == 1) return launch_stage_t<P, real, VISC, SGS, LDG, E0, 128>(dm, X, st, o, r1, r2, ms);
+  const Tiles tl = tiles_of(dm);
+  if (tl.epb == 0) {
+    if (tl.fbs == 0) return launch_stage_t<P, real, VISC, SGS, LDG, E0, 256>(dm, X, st, o, r1, r2, ms);
+    if (tl.fbs == 1) return launch_stage_t<P, real, VISC, SGS, LDG, E0, 128>(dm, X, st, o, r1, r2, ms);
     return launch_stage_t<P, real, VISC, SGS, LDG, E0, 64>(dm, X, st, o, r1, r2, ms);
   }
-  if (dm.tile_fbs == 0) return launch_stage_t<P, real, VISC, SGS, LDG, E1, 256>(dm, X, st, o, r1, r2, ms);
-  if (dm.tile_fbs == 1) return launch_stage_t<P, real, VISC, SGS, LDG, E1, 128>(dm, X, st, o, r1, r2, ms);
+  if (tl.fbs == 0) return launch_stage_t<P, real, VISC, SGS, LDG, E1, 256>(dm, X, st, o, r1, r2, ms);
+  if (tl.fbs == 1) return launch_stage_t<P, real, VISC, SGS, LDG, E1, 128>(dm, X, st, o, r1, r2, ms);
   return launch_stage_t<P, real, VISC, SGS, LDG, E1, 64>(dm, X, st, o, r1, r2, ms);
 }
 
@@ -1251,6 +1252,7 @@ void frk::stage_setup(DeviceMesh &dm, int scheme, int s, double dt, StageArgs &s
   if (scheme == FR_LSRK45) {
     st.mode = kModeLSRK;
     st.first = s == 0;
+    st.last = s == 4;
     st.a = kLsA[s];
     st.b = kLsB[s];
   } else if (scheme == FR_RK4) {
@@ -1629,6 +1631,7 @@ int fr_set_tiles(fr_mesh_t m, int32_t epb, int32_t fbs) {
   if (epb < 0 || epb > 1 || fbs < 0 || fbs > 2) return fail(FR_ERR_ARG, "epb must be 0..1 and fbs 0..2");
   m->dm.tile_epb = epb;
   m->dm.tile_fbs = fbs;
+  m->dm.tiles_set = true;
   return FR_OK;
 }
 
@@ -1662,6 +1665,7 @@ int fr_autotune(fr_mesh_t m, int n_trials, double *ms) {
   if (hipMemsetAsync(tmp2, 0, M * sizeof(double), s) != hipSuccess) rc = fail(FR_ERR_HIP, "hipMemsetAsync");
   if (rc == FR_OK && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess))
     rc = fail(FR_ERR_HIP, "hipEventCreate");
+  dm.tiles_set = true;
   for (int c = 0; c < 12 && rc == FR_OK; ++c) {
     dm.tile_epb = (c % 6) / 3;
     dm.tile_fbs = c % 3;

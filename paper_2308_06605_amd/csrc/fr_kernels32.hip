@@ -949,13 +949,14 @@ template <int P, bool VISC>
 int launch32_tiles(DeviceMesh &dm, const double *X, StageArgs st, double *o, double *r1, double *r2, double *ms,
                    std::string &err) {
   constexpr int E0 = Cfg<P>::EPB, E1 = Cfg<P>::EPB2;
-  if (dm.tile_epb == 0) {
-    if (dm.tile_fbs == 0) return launch32_t<P, VISC, E0, 256>(dm, X, st, o, r1, r2, ms, err);
-    if (dm.tile_fbs == 1) return launch32_t<P, VISC, E0, 128>(dm, X, st, o, r1, r2, ms, err);
+  const Tiles tl = tiles_of(dm);
+  if (tl.epb == 0) {
+    if (tl.fbs == 0) return launch32_t<P, VISC, E0, 256>(dm, X, st, o, r1, r2, ms, err);
+    if (tl.fbs == 1) return launch32_t<P, VISC, E0, 128>(dm, X, st, o, r1, r2, ms, err);
     return launch32_t<P, VISC, E0, 64>(dm, X, st, o, r1, r2, ms, err);
   }
-  if (dm.tile_fbs == 0) return launch32_t<P, VISC, E1, 256>(dm, X, st, o, r1, r2, ms, err);
-  if (dm.tile_fbs == 1) return launch32_t<P, VISC, E1, 128>(dm, X, st, o, r1, r2, ms, err);
+  if (tl.fbs == 0) return launch32_t<P, VISC, E1, 256>(dm, X, st, o, r1, r2, ms, err);
+  if (tl.fbs == 1) return launch32_t<P, VISC, E1, 128>(dm, X, st, o, r1, r2, ms, err);
   return launch32_t<P, VISC, E1, 64>(dm, X, st, o, r1, r2, ms, err);
 }
 
