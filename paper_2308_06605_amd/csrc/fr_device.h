@@ -137,6 +137,33 @@ __device__ __forceinline__ void visc_flux(const real U[5], const real G[3][5], c
 }
 
 // ------------------------------------------------------------------------------------------
+// Memory accesses by reuse
+// ------------------------------------------------------------------------------------------
+// Loads of data that a kernel reads once in all: the face buffers and face geometry in the face
+// kernels (each entry belongs to one face), the RK register in the volume kernels (also stored that
+// way). Non-temporal, they leave the caches to what is read again: the metric terms, which the fused
+// pre-pass reloads, and the face results, which both neighbours read. Only where a wave's runs of
+// RUN values are whole 128-byte lines or halves: shorter or ragged runs share lines with their
+// neighbours, and a line dropped after its first use is fetched again. Two LSRK45 steps (us): 40^3
+// p=3 FP64 6515 -> 6342 with the face values and gradients, -> 6306 with the face geometry, -> 6256
+// with the register, FP32 form 4944 -> 4890; 16^3 p=7 FP64 2732 -> 2575, FP32 2040 -> 1937; but with
+// ragged runs 27x25x29 p=2 FP64 (72 bytes) 1183 -> 1331, 13x11x17 p=5 FP32 (144) 524 -> 541. The same
+// hint on the metric terms or on the face results, stored or loaded, loses at 40^3 p=3 (6573, 6520,
+// 6600 against 6342).
+template <int RUN, typename T>
+constexpr bool kWholeRun = RUN * (int)sizeof(T) % 128 == 0 || RUN * (int)sizeof(T) == 64;
+template <int RUN, typename T>
+__device__ __forceinline__ T load_once(const T *p) {
+  if constexpr (kWholeRun<RUN, T>) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <int RUN, typename T>
+__device__ __forceinline__ void store_once(T v, T *p) {
+  if constexpr (kWholeRun<RUN, T>) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+// ------------------------------------------------------------------------------------------
 // Fused epilogue of the volume kernels: the source term and the RK register update of one
 // point, in double precision.
 // ------------------------------------------------------------------------------------------
@@ -159,6 +186,7 @@ __device__ __forceinline__ double body_force(const StageArgs &st, const double X
 //             q2 <- q2/25 + 9/25 q1, q1 <- 15 q2 - 5 q1; stage 9 sets q1 <- q2 + 3/5 q1 + dt/10 R.
 // Returns the value of the state the next stage is evaluated on (RK4: S, or Q after the last
 // stage; the others: U), which the volume kernel's fused pre-pass of the next stage uses.
+template <int NS>
 __device__ __forceinline__ double rk_store(const StageArgs &st, int64_t o, double x, double R, double r1,
                                            double r2, double *out0, double *reg1, double *reg2) {
   if (st.mode == kModeResidual) {
@@ -168,7 +196,7 @@ __device__ __forceinline__ double rk_store(const StageArgs &st, int64_t o, doubl
   if (st.mode == kModeLSRK) {
     const double du = fma(st.a, r1, st.dt * R);
     const double u = fma(st.b, du, x);
-    if (!st.last) reg1[o] = du;
+    if (!st.last) store_once<NS>(du, &reg1[o]);
     out0[o] = u;
     return u;
   }
@@ -176,7 +204,7 @@ __device__ __forceinline__ double rk_store(const StageArgs &st, int64_t o, doubl
     const double acc = fma(st.w, R, r1);
     if (!st.last) {
       const double sn = fma(st.cdt, R, r2);
-      reg1[o] = acc;
+      store_once<NS>(acc, &reg1[o]);
       reg2[o] = sn;
       return sn;
     }

@@ -196,10 +196,10 @@ __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const 
   real UL[5], UR[5], UC[5];
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
-    UL[v] = srcL[v * NFP];
-    UR[v] = srcR[v * NFP];
+    UL[v] = load_once<NFP>(&srcL[v * NFP]);
+    UR[v] = load_once<NFP>(&srcR[v * NFP]);
   }
-  const real NL[3] = {fg[0], fg[NFP], fg[2 * NFP]};
+  const real NL[3] = {load_once<NFP>(&fg[0]), load_once<NFP>(&fg[NFP]), load_once<NFP>(&fg[2 * NFP])};
   const real nm = sqrt(NL[0] * NL[0] + NL[1] * NL[1] + NL[2] * NL[2]);
   const real inm = real(1) / nm;
   const real nh[3] = {NL[0] * inm, NL[1] * inm, NL[2] * inm};
@@ -209,13 +209,13 @@ __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const 
   if (VISC) {
     // BR2: mean of the broken gradients plus the two face liftings, which combine to
     // sigma N (U_R - U_L) with N the owner's normal
-    const real sig = fg[3 * NFP];
+    const real sig = load_once<NFP>(&fg[3 * NFP]);
     real GI[3][5];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int v = 0; v < 5; ++v)
-        GI[i][v] = real(0.5) * (srcL[(5 + i * 5 + v) * NFP] + srcR[(5 + i * 5 + v) * NFP]) +
+        GI[i][v] = real(0.5) * (load_once<NFP>(&srcL[(5 + i * 5 + v) * NFP]) + load_once<NFP>(&srcR[(5 + i * 5 + v) * NFP])) +
                    sig * NL[i] * (UR[v] - UL[v]);
     real Fv[3][5];
     real mu = ph.mu, kap = ph.kappa;
@@ -437,11 +437,11 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
     // costs the gradient phase its registers)
     if (st.mode == kModeLSRK) {
 #pragma unroll
-      for (int v = 0; v < 5; ++v) r1[v] = st.first ? 0.0 : reg1[base + v * NS];
+      for (int v = 0; v < 5; ++v) r1[v] = st.first ? 0.0 : load_once<NS>(&reg1[base + v * NS]);
     } else if (st.mode == kModeRK4) {
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        r1[v] = st.first ? 0.0 : reg1[base + v * NS];
+        r1[v] = st.first ? 0.0 : load_once<NS>(&reg1[base + v * NS]);
         r2[v] = out0[base + v * NS];
       }
     } else if (st.mode == kModeSSP) {
@@ -498,7 +498,7 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       const double R = -double(div[v]) * double(iJ) + body_force(st, Xd, v);
-      const double xn = rk_store(st, base + v * NS, Xd[v], R, r1[v], r2[v], out0, reg1, reg2);
+      const double xn = rk_store<NS>(st, base + v * NS, Xd[v], R, r1[v], r2[v], out0, reg1, reg2);
       if (PRE) sU[v * NS + t] = real(xn);
     }
   }

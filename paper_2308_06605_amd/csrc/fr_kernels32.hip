@@ -320,12 +320,13 @@ __device__ __forceinline__ void face32_body(unsigned blk, const float *__restric
   float UL[5], UR[5];
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
-    UL[v] = srcL[v * NFP];
-    UR[v] = srcR[v * NFP];
+    UL[v] = load_once<NFP>(&srcL[v * NFP]);
+    UR[v] = load_once<NFP>(&srcR[v * NFP]);
   }
-  const double Nd[3] = {fg[0], fg[NFP], fg[2 * NFP]};
+  const double Nd[3] = {load_once<NFP>(&fg[0]), load_once<NFP>(&fg[NFP]), load_once<NFP>(&fg[2 * NFP])};
   // central mass flux in FP64: (m_L + m_R)/2 . N
-  const double fc_rho = 0.5 * ((mL[0] + mR[0]) * Nd[0] + (mL[NFP] + mR[NFP]) * Nd[1] + (mL[2 * NFP] + mR[2 * NFP]) * Nd[2]);
+  const double fc_rho = 0.5 * ((load_once<NFP>(&mL[0]) + load_once<NFP>(&mR[0])) * Nd[0] + (load_once<NFP>(&mL[NFP]) + load_once<NFP>(&mR[NFP])) * Nd[1] +
+                               (load_once<NFP>(&mL[2 * NFP]) + load_once<NFP>(&mR[2 * NFP])) * Nd[2]);
   const float NL[3] = {float(Nd[0]), float(Nd[1]), float(Nd[2])};
   const float nm = sqrtf(NL[0] * NL[0] + NL[1] * NL[1] + NL[2] * NL[2]);
   const float inm = 1.0f / nm;
@@ -333,13 +334,13 @@ __device__ __forceinline__ void face32_body(unsigned blk, const float *__restric
   float Fr[5];
   riemann32(UL, UR, nh, ph, ref, flux, Fr);
   if (VISC) {
-    const float sig = float(fg[3 * NFP]);
+    const float sig = float(load_once<NFP>(&fg[3 * NFP]));
     float GI[3][5];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int v = 0; v < 5; ++v)
-        GI[i][v] = 0.5f * (srcL[(5 + i * 5 + v) * NFP] + srcR[(5 + i * 5 + v) * NFP]) + sig * NL[i] * (UR[v] - UL[v]);
+        GI[i][v] = 0.5f * (load_once<NFP>(&srcL[(5 + i * 5 + v) * NFP]) + load_once<NFP>(&srcR[(5 + i * 5 + v) * NFP])) + sig * NL[i] * (UR[v] - UL[v]);
     float UCp[5], UC[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) UCp[v] = 0.5f * (UL[v] + UR[v]);
@@ -553,11 +554,11 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
     // costs the gradient phase its registers)
     if (st.mode == kModeLSRK) {
 #pragma unroll
-      for (int v = 0; v < 5; ++v) r1[v] = st.first ? 0.0 : reg1[base + v * NS];
+      for (int v = 0; v < 5; ++v) r1[v] = st.first ? 0.0 : load_once<NS>(&reg1[base + v * NS]);
     } else if (st.mode == kModeRK4) {
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        r1[v] = st.first ? 0.0 : reg1[base + v * NS];
+        r1[v] = st.first ? 0.0 : load_once<NS>(&reg1[base + v * NS]);
         r2[v] = out0[base + v * NS];
       }
     } else if (st.mode == kModeSSP) {
@@ -627,7 +628,7 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       const double xn =
-          rk_store(st, base + v * NS, Xd[v], Rv[v] + body_force(st, Xd, v), r1[v], r2[v], out0, reg1, reg2);
+          rk_store<NS>(st, base + v * NS, Xd[v], Rv[v] + body_force(st, Xd, v), r1[v], r2[v], out0, reg1, reg2);
       if (PRE) {
         sU[v * NS + t] = v == 0 ? float(xn - ref.rho_d) : (v == 4 ? float(xn - ref.E_d) : float(xn));
         if (v >= 1 && v <= 3) xm[v - 1] = xn;
