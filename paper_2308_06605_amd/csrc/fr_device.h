@@ -348,7 +348,7 @@ __device__ __forceinline__ int plane_index(int t) {
 }
 
 // Interpolation to both faces normal to direction d: the sums over the line through their face
-// point (a, b) of lm[c] src[line_pt(d, c, a, b)] and lp[c] src[...], the line read once for the
+// point (a, b), c along it, of lm[c] src[point c] and lp[c] src[point c], the line read once for the
 // two. d must be the same on every lane of the wavefront (the p = 7 kernels give each wavefront
 // one direction's 64 lines); it picks one of three loops whose LDS strides are constants.
 // * In ascending c (ROT false, and d = 2 always) lm and lp are read through scalar loads. For
@@ -430,13 +430,6 @@ __device__ __forceinline__ void face_sums_uniform(int d, int a, int b, const T *
 // per block, where the kernels take their face loops as wave-uniform (value, face) tasks.
 template <int NFP, int EPB>
 constexpr bool kWavePerFace = NFP == 64 && EPB == 1;
-
-// index of solution point with coordinate c along direction d and (a, b) along the face's
-// tangential directions (increasing axis order)
-template <int N>
-__device__ __forceinline__ int line_pt(int d, int c, int a, int b) {
-  return d == 0 ? c + N * (a + N * b) : (d == 1 ? a + N * (c + N * b) : a + N * (b + N * c));
-}
 
 // The face values of NV point-ordered element arrays (array v at src + v N_s): every line of
 // points normal to a pair of faces is read once and gives the values at both its ends, with

@@ -36,14 +36,6 @@ struct SgsOps {
   double w[kMaxN];
 };
 
-struct Ops1Df {
-  float D[kMaxN * kMaxN];
-  float lm[kMaxN];
-  float lp[kMaxN];
-  float gcL[kMaxN];
-  float gcR[kMaxN];
-};
-
 // Per element face: packed neighbour information.
 //   nbr   : neighbour element index
 //   code  : bits 0-2 neighbour's local face, bit 3 swap, bit 4 flip u, bit 5 flip v,
@@ -115,7 +107,6 @@ struct DeviceMesh {
   double eta;
   Physics phys;
   Ops1D ops;
-  Ops1Df opsf;
   // state registers [E][5][Ns] doubles
   double *U = nullptr;   // solution (LSRK: U; RK4: Q)
   double *R1 = nullptr;  // LSRK: dU; RK4: accumulator

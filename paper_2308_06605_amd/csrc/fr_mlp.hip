@@ -48,15 +48,6 @@ __device__ __forceinline__ unsigned short bf16_bits(float x) {
 }
 __device__ __forceinline__ float bf16_val(unsigned short b) { return __uint_as_float((unsigned)b << 16); }
 
-__device__ __forceinline__ void split4(const float x[4], v4s &hi, v4s &lo) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const unsigned short h = bf16_bits(x[i]);
-    hi[i] = (short)h;
-    lo[i] = (short)bf16_bits(x[i] - bf16_val(h));
-  }
-}
-
 __device__ __forceinline__ v4f mfma(v4s a, v4s b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
