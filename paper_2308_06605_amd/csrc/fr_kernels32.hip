@@ -386,7 +386,8 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
   constexpr int R = (NF + NS - 1) / NS;
   // with the fused pre-pass at p <= 6 (SP) the tail takes one pass: sJ and sM are enlarged to
   // hold the whole gradient (15 N_s) and the three momentum components (measured: faster than
-  // the rounds below by 27% at p = 4 and 6% at p = 6; at p = 7 the larger LDS costs 3%)
+  // the rounds below by 27% at p = 4 and 6% at p = 6; at p = 7 its 78 KB gain nothing: two
+  // LSRK45 steps at 16^3 take 1935 us against 1936)
   constexpr bool SP = PRE && P <= 6;
   constexpr int NJ0 = (VISC ? 9 : 4) * NF;  // [4][NF] flux (mom 3, reduced energy), [5][NF] jumps
   constexpr int NJ = SP && VISC && 15 * NS > NJ0 ? 15 * NS : NJ0;
