@@ -328,10 +328,14 @@ __device__ __forceinline__ void elem_sync() {
 // p=3) except where a run is shorter than a 128-byte line and does not divide it (doubles at
 // p = 2, floats at p = 2 and 4): there consecutive runs share lines, and plain stores let L2
 // merge the pieces (the p = 2 pre-pass 3.56 -> 1.52 ms at 80^3).
-template <int NFP, typename T>
+// MERGE: plain stores also for runs longer than a line that end inside one (p = 4, 5, 6). The
+// pre-pass and the face kernels take them: at 52^3 p = 4 FP64 1.14 -> 1.04 ms and 0.98 -> 0.90, at
+// 43^3 p = 5 FP32 form 0.64 -> 0.59 and 0.48 -> 0.47. The fused tail does not: there they measured
+// 1.57 -> 1.62 ms and 1.27 -> 1.28.
+template <int NFP, bool MERGE = false, typename T>
 __device__ __forceinline__ void face_store(T v, T *p) {
   constexpr int run = NFP * (int)sizeof(T);
-  if constexpr (run >= 128 || 128 % run == 0) {
+  if constexpr (run % 128 == 0 || 128 % run == 0 || (run > 128 && !MERGE)) {
     __builtin_nontemporal_store(v, p);
   } else {
     *p = v;
@@ -438,7 +442,7 @@ constexpr bool kWavePerFace = NFP == 64 && EPB == 1;
 // store consecutive points of a face. GV: few arrays per item where an item per line would leave
 // many threads idle (N^2 lines of NV / GV items over N^3 threads). dst: the element's first face
 // entry, [6][nval][NFP]; array v goes to its entry slot(v), which steps by one within an item.
-template <int N, int NV, int GV, typename T, typename C, typename Slot>
+template <int N, int NV, int GV, bool MERGE = false, typename T, typename C, typename Slot>
 __device__ __forceinline__ void write_traces(int t, const T *src, const C *lm, const C *lp, T *dst, int nval, Slot slot) {
   constexpr int NFP = N * N, NS = N * N * N, ITEMS = NV / GV * NFP;
   static_assert(NV % GV == 0, "arrays per item");
@@ -457,8 +461,8 @@ __device__ __forceinline__ void write_traces(int t, const T *src, const C *lm, c
           lo = fma(lm[c], y, lo);
           hi = fma(lp[c], y, hi);
         }
-        face_store<NFP>(lo, &out[v * NFP]);
-        face_store<NFP>(hi, &out[(nval + v) * NFP]);
+        face_store<NFP, MERGE>(lo, &out[v * NFP]);
+        face_store<NFP, MERGE>(hi, &out[(nval + v) * NFP]);
       }
     }
   }

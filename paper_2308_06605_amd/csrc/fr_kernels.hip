@@ -108,7 +108,7 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_PREPASS(P)) v
       face_store<NFP>(hi, &dst[((2 * d + 1) * 20 + val) * NFP + lane]);
     }
   } else {
-    write_traces<N, NVAL, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
+    write_traces<N, NVAL, kTraceGroup<N>, true>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
   }
 }
 
@@ -235,8 +235,8 @@ __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const 
   real *dst = fout + (fc * 10) * NFP + kk;
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
-    face_store<NFP>(real(0.5) * (UR[v] - UL[v]), &dst[v * NFP]);  // U^C - U_L
-    face_store<NFP>(nm * (Fi[v] - Fvn[v]), &dst[(5 + v) * NFP]);
+    face_store<NFP, true>(real(0.5) * (UR[v] - UL[v]), &dst[v * NFP]);  // U^C - U_L
+    face_store<NFP, true>(nm * (Fi[v] - Fvn[v]), &dst[(5 + v) * NFP]);
   }
 }
 

@@ -219,8 +219,8 @@ __device__ __forceinline__ void prepass32_body(unsigned blk, const double *__res
       }
     }
   } else {
-    write_traces<N, NV, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
-    write_traces<N, 3, 1>(t, sM, opsd.lm, opsd.lp, dm, 3, [](int v) { return v; });
+    write_traces<N, NV, kTraceGroup<N>, true>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
+    write_traces<N, 3, 1, true>(t, sM, opsd.lm, opsd.lp, dm, 3, [](int v) { return v; });
   }
 }
 
@@ -352,9 +352,9 @@ __device__ __forceinline__ void face32_body(unsigned blk, const float *__restric
   }
   float *dst = fout32 + (fc * 9) * NFP + kk;
 #pragma unroll
-  for (int v = 0; v < 5; ++v) face_store<NFP>(0.5f * (UR[v] - UL[v]), &dst[v * NFP]);
+  for (int v = 0; v < 5; ++v) face_store<NFP, true>(0.5f * (UR[v] - UL[v]), &dst[v * NFP]);
 #pragma unroll
-  for (int v = 1; v < 5; ++v) face_store<NFP>(nm * Fr[v], &dst[(4 + v) * NFP]);
+  for (int v = 1; v < 5; ++v) face_store<NFP, true>(nm * Fr[v], &dst[(4 + v) * NFP]);
   __builtin_nontemporal_store(fc_rho + double(nm * Fr[0]), &foutm[fc * NFP + kk]);
 }
 
