@@ -442,8 +442,9 @@ constexpr bool kWavePerFace = NFP == 64 && EPB == 1;
 // store consecutive points of a face. GV: few arrays per item where an item per line would leave
 // many threads idle (N^2 lines of NV / GV items over N^3 threads). dst: the element's first face
 // entry, [6][nval][NFP]; array v goes to its entry slot(v), which steps by one within an item.
-template <int N, int NV, int GV, bool MERGE = false, typename T, typename C, typename Slot>
-__device__ __forceinline__ void write_traces(int t, const T *src, const C *lm, const C *lp, T *dst, int nval, Slot slot) {
+// PIECES: plain stores (see kPieceElems).
+template <int N, int NV, int GV, bool MERGE, bool PIECES, typename T, typename C, typename Slot>
+__device__ __forceinline__ void trace_lines(int t, const T *src, const C *lm, const C *lp, T *dst, int nval, Slot slot) {
   constexpr int NFP = N * N, NS = N * N * N, ITEMS = NV / GV * NFP;
   static_assert(NV % GV == 0, "arrays per item");
 #pragma unroll
@@ -461,11 +462,39 @@ __device__ __forceinline__ void write_traces(int t, const T *src, const C *lm, c
           lo = fma(lm[c], y, lo);
           hi = fma(lp[c], y, hi);
         }
-        face_store<NFP, MERGE>(lo, &out[v * NFP]);
-        face_store<NFP, MERGE>(hi, &out[(nval + v) * NFP]);
+        if constexpr (PIECES) {
+          out[v * NFP] = lo;
+          out[(nval + v) * NFP] = hi;
+        } else {
+          face_store<NFP, MERGE>(lo, &out[v * NFP]);
+          face_store<NFP, MERGE>(hi, &out[(nval + v) * NFP]);
+        }
       }
     }
   }
+}
+// At p = 0 and 1 a run is 4 to 32 bytes, a piece of a line that an item fills over several of its
+// stores, for both ends of its lines in turn. Stored non-temporally the pieces go to memory as
+// pieces; through the cache the lines leave whole, which is the better on all but small meshes.
+// kPieceElems: the element count up to which p = 1 stores non-temporally all the same. Two LSRK45
+// steps (us), non-temporal / through the cache: p = 0 FP64 8000 elements 193 / 169, 24389 657 / 307,
+// 54872 1576 / 533; FP32 form 8000 137 / 148, 24389 426 / 269, 54872 1017 / 388; p = 1 FP64 3375
+// 183 / 193, 5832 278 / 250, 15625 600 / 412, 29791 1007 / 736; FP32 form 3375 161 / 178, 5832
+// 246 / 245, 15625 542 / 374, 29791 962 / 678.
+constexpr int64_t kPieceElems = 5500;
+template <int N, int NV, int GV, bool MERGE = false, typename T, typename C, typename Slot>
+__device__ __forceinline__ void write_traces(int64_t E, int t, const T *src, const C *lm, const C *lp, T *dst, int nval,
+                                             Slot slot) {
+  if constexpr (N <= 2) {
+    if (N == 1 || E > kPieceElems) {
+      // (the empty statements keep the compiler from joining the two branches' stores as plain ones)
+      asm volatile("" ::: "memory");
+      trace_lines<N, NV, GV, MERGE, true>(t, src, lm, lp, dst, nval, slot);
+      asm volatile("" ::: "memory");
+      return;
+    }
+  }
+  trace_lines<N, NV, GV, MERGE, false>(t, src, lm, lp, dst, nval, slot);
 }
 // Arrays per item for 20 arrays: 5 where (20 / 5) N^2 items fill the N^3 threads, else 1.
 template <int N>

@@ -108,7 +108,7 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_PREPASS(P)) v
       face_store<NFP>(hi, &dst[((2 * d + 1) * 20 + val) * NFP + lane]);
     }
   } else {
-    write_traces<N, NVAL, kTraceGroup<N>, true>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
+    write_traces<N, NVAL, kTraceGroup<N>, true>(E, t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
   }
 }
 
@@ -567,7 +567,7 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
       gradient(0, 5);
     }
     elem_sync<NS>();
-    if (act) write_traces<N, 20, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
+    if (act) write_traces<N, 20, kTraceGroup<N>>(E, t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
     return;
   }
   // several chunks (p >= 6): the traces of the values, then of the gradient chunk by chunk
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
   };
   if (act) {
     if constexpr (kWavePerFace<NFP, EPB>) tasks(sU, 5, [](int v) { return v; });
-    else write_traces<N, 5, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
+    else write_traces<N, 5, kTraceGroup<N>>(E, t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
   }
   if constexpr (GRAD) {
     // (the metric terms are loaded after the values pass, so they are not live across it)
@@ -599,8 +599,8 @@ __global__ __launch_bounds__(EPBX * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_VOLUME(P, SGS
         // component ci = ii * nv + w of the chunk is d/dx_ii of variable v0 + w
         auto slot_of = [&](int ci) { return 5 + (ci / nv) * 5 + v0 + ci % nv; };
         if constexpr (kWavePerFace<NFP, EPB>) tasks(sJ, 3 * nv, slot_of);
-        else if (nv == VPC) write_traces<N, 3 * VPC, 1>(t, sJ, ops.lm, ops.lp, dst, 20, slot_of);
-        else write_traces<N, 3 * (5 - VPC * (NCH - 1)), 1>(t, sJ, ops.lm, ops.lp, dst, 20, slot_of);
+        else if (nv == VPC) write_traces<N, 3 * VPC, 1>(E, t, sJ, ops.lm, ops.lp, dst, 20, slot_of);
+        else write_traces<N, 3 * (5 - VPC * (NCH - 1)), 1>(E, t, sJ, ops.lm, ops.lp, dst, 20, slot_of);
       }
       elem_sync<NS>();
     }

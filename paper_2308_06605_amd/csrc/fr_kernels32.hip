@@ -219,8 +219,8 @@ __device__ __forceinline__ void prepass32_body(unsigned blk, const double *__res
       }
     }
   } else {
-    write_traces<N, NV, kTraceGroup<N>, true>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
-    write_traces<N, 3, 1, true>(t, sM, opsd.lm, opsd.lp, dm, 3, [](int v) { return v; });
+    write_traces<N, NV, kTraceGroup<N>, true>(E, t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
+    write_traces<N, 3, 1, true>(E, t, sM, opsd.lm, opsd.lp, dm, 3, [](int v) { return v; });
   }
 }
 
@@ -700,8 +700,8 @@ __device__ __forceinline__ void volume32_body(unsigned blk,
     }
     elem_sync<NS>();
     if (act) {
-      write_traces<N, VISC ? 20 : 5, kTraceGroup<N>>(t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
-      write_traces<N, 3, 1>(t, sM, opsd.lm, opsd.lp, dm, 3, [](int v) { return v; });
+      write_traces<N, VISC ? 20 : 5, kTraceGroup<N>>(E, t, sU, ops.lm, ops.lp, dst, 20, [](int v) { return v; });
+      write_traces<N, 3, 1>(E, t, sM, opsd.lm, opsd.lp, dm, 3, [](int v) { return v; });
     }
     return;
   }
