@@ -269,6 +269,11 @@ struct Cfg {
 #ifndef FR_WPE_LDG
 #define FR_WPE_LDG(P) ((P) <= 5 ? 3 : 2)
 #endif
+// The feature kernel at p = 6: left alone the compiler takes 130 VGPRs, two too many for 4 waves
+// (us: 343 elements 13.8 -> 11.0, 729 20.5 -> 17.6, 1728 45.6 -> 38.8).
+#ifndef FR_WPE_FEATURES
+#define FR_WPE_FEATURES(P) ((P) == 6 ? 4 : 0)
+#endif
 #ifndef FR_WPE_VOLUME32
 #define FR_WPE_VOLUME32(P, PRE) ((P) == 7 || ((P) == 5 && !(PRE)) ? 4 : ((P) >= 2 && (PRE) ? 5 : 0))
 #endif

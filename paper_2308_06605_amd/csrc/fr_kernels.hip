@@ -780,7 +780,8 @@ __global__ __launch_bounds__(kLdgElems<P> * Cfg<P>::NS) FR_WPE_ATTR(FR_WPE_LDG(P
 // Bound by the instructions issued: FP64 logarithms and divisions, and pow. The invariants of all of
 // a block's elements are therefore finished by one wave, a lane per element and invariant, with one
 // logarithm and two divisions for the five (each element's first lane did them all, one after the
-// other, with the other lanes of its wave idle). 16^3 p=3 (us): 16.4 -> 10.7.
+// other, with the other lanes of its wave idle). 16^3 p=3 (us): 16.4 -> 10.7. At p = 0, where every
+// lane is an element's first, each does its own (29^3: 4.1 us; spread over items 7.8).
 // ------------------------------------------------------------------------------------------
 // x + (x of lane t + H), for the lanes t < H of a tree over a wave: the DPP row shifts within 16
 // lanes, a lane permutation above.
@@ -797,7 +798,7 @@ __device__ __forceinline__ double wave_tree_add(double x) {
 }
 
 template <int P>
-__global__ __launch_bounds__(Cfg<P>::BLOCK) void k_sgs_features(const double *__restrict__ X,
+__global__ __launch_bounds__(Cfg<P>::BLOCK) FR_WPE_ATTR(FR_WPE_FEATURES(P)) void k_sgs_features(const double *__restrict__ X,
                                                                  const double *__restrict__ geo, int64_t E,
                                                                  OpsT<double> ops, SgsOps so,
                                                                  float *__restrict__ feat) {
@@ -929,21 +930,24 @@ __global__ __launch_bounds__(Cfg<P>::BLOCK) void k_sgs_features(const double *__
   }
   __syncthreads();
   // item k < 5 of element es: invariant k + 1 over the volume (k = 0: s2, 1: w2, 2: r, 3: th, 4: th2)
-  for (int i = threadIdx.x; i < EPB * 5; i += EPB * NS) {
-    const int es = i / 5, k = i - 5 * es;
-    const int64_t ee = (int64_t)blockIdx.x * EPB + es;
-    if (ee < E) {
-      const double vol = sS[es][0], eps = 1e-12;
-      const double x = sS[es][k + 1] / vol;
-      float out;
-      if (k < 2) {
-        out = (float)(0.5 * log(x + eps));
-      } else {
-        const double s2e = sS[es][1] / vol + eps;
-        const double den = k == 2 ? pow(s2e, 1.5) : (k == 3 ? sqrt(s2e) : s2e);
-        out = (float)(x / den);
-      }
-      feat[ee * NFT + NS - 1 + k] = out;
+  auto invariant = [&](int es, int k) {
+    const double vol = sS[es][0], eps = 1e-12;
+    const double x = sS[es][k + 1] / vol;
+    if (k < 2) return (float)(0.5 * log(x + eps));
+    const double s2e = sS[es][1] / vol + eps;
+    const double den = k == 2 ? pow(s2e, 1.5) : (k == 3 ? sqrt(s2e) : s2e);
+    return (float)(x / den);
+  };
+  if constexpr (NS == 1) {
+    if (act) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) feat[e * NFT + k] = invariant(slot, k);
+    }
+  } else {
+    for (int i = threadIdx.x; i < EPB * 5; i += EPB * NS) {
+      const int es = i / 5, k = i - 5 * es;
+      const int64_t ee = (int64_t)blockIdx.x * EPB + es;
+      if (ee < E) feat[ee * NFT + NS - 1 + k] = invariant(es, k);
     }
   }
 }
