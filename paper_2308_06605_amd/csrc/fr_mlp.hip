@@ -19,6 +19,7 @@
 // deterministic.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -455,7 +456,13 @@ NetArgs args_of(const Net &n) {
   return a;
 }
 
-constexpr int64_t kMaxBlocks = 1 << 20;  // of an evaluation; blocks loop over the samples beyond
+// Blocks of an evaluation: at most as many as the chip holds at once (by its registers a CU holds 6
+// blocks of the kernel for up to 16 inputs, 5 up to 80, 4 above); they loop over the samples beyond,
+// with their weights loaded once. Per sample a block for every 16 costs more than the wave for every
+// 16 that loaded all the weights did where the inputs are few. 65536 samples (us), that wave / a
+// block for every 16 / these blocks: 5 inputs 12.4 / 14.6 / 11.4, 31 15.0 / 17.4 / 15.2, 68
+// 20.7 / 19.5 / 17.0, 128 40.2 / 33.0 / 22.8.
+constexpr int64_t eval_blocks(int kt) { return 256 * (kt == 1 ? 6 : (kt <= 5 ? 5 : 4)); }
 
 // Blocks of the training pass over n samples: one per 16 samples up to a block per CU.
 constexpr int64_t train_parts(int64_t n) {
@@ -469,7 +476,7 @@ int launch_mlp(const Net &net, hipStream_t st, const float *X, int64_t n, int64_
                double nu_scale, const float *tgt, float *part = nullptr) {
   const NetArgs a = args_of(net);
   const int64_t chunks = (n + kChunk - 1) / kChunk;
-  const unsigned blocks = (unsigned)(TRAIN ? train_parts(n) : (chunks < kMaxBlocks ? chunks : kMaxBlocks));
+  const unsigned blocks = (unsigned)(TRAIN ? train_parts(n) : std::min(chunks, eval_blocks(net.FP / 16)));
   const float inv_n = 1.f / (float)n;
   switch (net.FP / 16) {
 #define CASE(K)                                                                                                  \
