@@ -145,11 +145,13 @@ int fr_get_state(fr_mesh_t m, double *U, int on_device);
  *   fbs  threads per block of the face kernel: 0 = 256, 1 = 128, 2 = 64 (with FR_LDG the face
  *        kernel works per element and has a block of its own).
  * Until one is chosen (fr_get_tiles then gives 0, 0) a single mesh's stages take blocks by its size:
- * small meshes the smaller ones.
+ * small meshes the smaller ones; fr_tiles_in_force gives the tiles they are launched with, chosen or
+ * by size. Multi-mesh groups of a batch take fr_get_tiles' values.
  * Results are bitwise independent of the tiles (every thread does the same arithmetic). A batch
  * captures the tiles in force at its creation. */
 int fr_set_tiles(fr_mesh_t m, int32_t epb, int32_t fbs);
 int fr_get_tiles(fr_mesh_t m, int32_t *epb, int32_t *fbs);
+int fr_tiles_in_force(fr_mesh_t m, int32_t *epb, int32_t *fbs);
 
 /* Autotuner: time each tile choice, with and without the fused pre-pass (fr_set_fusion), on
  * this mesh and state: n_trials LSRK stages each from the current state into scratch buffers

@@ -89,7 +89,12 @@ def run(n_mesh=48, steps=16, warmup=2, seed=0, walls=True, prec="fp32", autotune
         dts.append(stable_dt(s["n"], s["p"], s["mach"]))
     setup_s = time.time() - t0
     t0 = time.time()
-    tiles = [g.autotune(3)[0] if autotune else g.tiles() for g in meshes]
+    if autotune:
+        for g in meshes:
+            g.autotune(3)
+    # the tiles of each mesh's own stages, and those it has in the batch's multi-mesh groups (FP32 form)
+    alone = [g.tiles_in_force() for g in meshes]
+    tiles = [g.tiles() for g in meshes] if prec == "fp32" else alone
     fused = [g.fusion() for g in meshes]
     autotune_s = time.time() - t0
     dof = sum(g.E * g.Ns for g in meshes)
@@ -157,7 +162,8 @@ def run(n_mesh=48, steps=16, warmup=2, seed=0, walls=True, prec="fp32", autotune
         "tiles_chosen": {f"{e},{f}": sum(1 for t in tiles if tuple(t) == (e, f)) for e in (0, 1) for f in (0, 1, 2)},
         "fused_prepass": sum(fused),
         "multi_groups": len({(s["p"], fz, tuple(t)) for s, t, fz in zip(specs, tiles, fused)}),
-        "meshes": [dict(s, dt=dt, tiles=list(t), fused=fz) for s, dt, t, fz in zip(specs, dts, tiles, fused)],
+        "meshes": [dict(s, dt=dt, tiles=list(t), tiles_alone=list(a), fused=fz)
+                   for s, dt, t, a, fz in zip(specs, dts, tiles, alone, fused)],
     }
     return out
 

@@ -1646,6 +1646,14 @@ int fr_get_tiles(fr_mesh_t m, int32_t *epb, int32_t *fbs) {
   return FR_OK;
 }
 
+int fr_tiles_in_force(fr_mesh_t m, int32_t *epb, int32_t *fbs) {
+  if (!valid(m)) return fail(FR_ERR_ARG, "not a mesh handle");
+  const Tiles tl = tiles_of(m->dm);
+  if (epb) *epb = tl.epb;
+  if (fbs) *fbs = tl.fbs;
+  return FR_OK;
+}
+
 int fr_autotune(fr_mesh_t m, int n_trials, double *ms) {
   if (!valid(m)) return fail(FR_ERR_ARG, "not a mesh handle");
   if (int rc = reject_part(m, "fr_autotune")) return rc;

@@ -79,6 +79,7 @@ def load():
     L.fr_set_body_force.argtypes = [P, P]
     L.fr_set_tiles.argtypes = [P, ctypes.c_int32, ctypes.c_int32]
     L.fr_get_tiles.argtypes = [P, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
+    L.fr_tiles_in_force.argtypes = [P, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
     L.fr_autotune.argtypes = [P, i32, P]
     L.fr_set_fusion.argtypes = [P, ctypes.c_int32]
     L.fr_get_fusion.argtypes = [P, ctypes.POINTER(ctypes.c_int32)]
@@ -121,7 +122,7 @@ def load():
                  "fr_get_state", "fr_residual", "fr_rk_step", "fr_mesh_info", "fr_profile_stages",
                  "fr_mesh_geometry_host", "fr_basis_host", "fr_rk_coefficients", "fr_kinetic_energy", "fr_sgs_n_features", "fr_set_body_force",
                  "fr_batch_create", "fr_batch_create_ex", "fr_batch_step", "fr_batch_set_stream", "fr_batch_destroy",
-                 "fr_set_tiles", "fr_get_tiles", "fr_autotune", "fr_set_fusion", "fr_get_fusion",
+                 "fr_set_tiles", "fr_get_tiles", "fr_tiles_in_force", "fr_autotune", "fr_set_fusion", "fr_get_fusion",
                  "fr_sgs_features", "fr_set_eddy_viscosity", "fr_set_sgs_model", "fr_get_eddy_viscosity",
                  "fr_mlp_create", "fr_mlp_destroy", "fr_mlp_set_stream", "fr_mlp_set_params",
                  "fr_mlp_get_params", "fr_mlp_get_bf16", "fr_mlp_forward", "fr_mlp_loss_grad",
@@ -346,6 +347,12 @@ class FRMesh:
     def tiles(self):
         e, f = ctypes.c_int32(), ctypes.c_int32()
         _check(load().fr_get_tiles(self.h, ctypes.byref(e), ctypes.byref(f)))
+        return e.value, f.value
+
+    def tiles_in_force(self):
+        """The tiles this mesh's own stages are launched with: tiles() once chosen, until then by size."""
+        e, f = ctypes.c_int32(), ctypes.c_int32()
+        _check(load().fr_tiles_in_force(self.h, ctypes.byref(e), ctypes.byref(f)))
         return e.value, f.value
 
     def autotune(self, n_trials: int = 3):

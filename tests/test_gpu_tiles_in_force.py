@@ -1,0 +1,50 @@
+"""The tiles a mesh's own stages are launched with: by size until some are chosen (tiles() gives (0, 0)
+all the while), then those chosen; and the batched workload's record, which names the tiles that
+ran."""
+import pytest
+
+from paper_2308_06605_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _fr():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2308_06605_amd import fr
+
+    fr.load()
+    return fr
+
+
+def test_by_size_then_chosen():
+    fr = _fr()
+    small, large = (fr.FRMesh(I.box_mesh(n, q=1), 3, mu=1e-3) for n in (4, 14))
+    assert small.tiles() == large.tiles() == (0, 0)
+    assert small.tiles_in_force() == (1, 2) and large.tiles_in_force() == (0, 0)
+    for t in [(0, 0), (0, 1), (1, 2)]:
+        small.set_tiles(*t)
+        assert small.tiles() == small.tiles_in_force() == t
+    large.set_tiles(*small.tiles_in_force())
+    assert large.tiles_in_force() == (1, 2)
+    tuned, _ = small.autotune(2)
+    assert small.tiles() == small.tiles_in_force() == tuned
+    small.close()
+    large.close()
+    with pytest.raises(fr.FRError):
+        fr._check(fr.load().fr_tiles_in_force(None, None, None))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_record_of_the_batched_workload(prec):
+    fr = _fr()
+    from paper_2308_06605_amd import batched
+
+    res = batched.run(n_mesh=3, steps=1, warmup=1, seed=0, prec=prec, autotune=False, sizes=(3, 5))
+    for m in res["meshes"]:
+        g, _ = batched.build(fr, m, True, prec)
+        assert tuple(m["tiles_alone"]) == g.tiles_in_force() != (0, 0)
+        assert tuple(m["tiles"]) == ((0, 0) if prec == "fp32" else g.tiles_in_force())
+        g.close()
