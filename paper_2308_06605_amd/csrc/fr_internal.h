@@ -234,21 +234,29 @@ inline int tile_elements(int Ns, int epb) {
 }
 // The tiles a single mesh's kernels are launched with: those chosen, or until then a choice by size.
 // Where half blocks still leave at most one per CU (256), they spread a small mesh over more of the
-// chip; face blocks of one wave do the same up to four waves per CU. Elements of 125 points (p = 4)
-// always take a block each (two waves meet at its barriers instead of four). Time per LSRK45 stage
-// (us), 256/N_s elements and 256 threads against the choice here: p=1 1000 elements 15.5 / 12.0, p=2
-// 343 15.4 / 13.6, p=3 125 14.5 / 12.3, p=4 64 15.9 / 13.7, p=4 2197 52.3 / 48.7 (FP64; FP32 form
-// 15.4 / 12.6, 15.6 / 14.1, 13.0 / 12.4, 14.4 / 13.4, 35.5 / 34.8); beyond the limits there is no
-// difference or a loss (p=2 2197 22.5 against 23.8 with half blocks). Multi-mesh groups keep
-// 256/N_s and 256.
+// chip; face blocks of one wave do the same up to two waves per CU. Blocks of two elements (p = 4)
+// leave the fullest CU an even number of elements, blocks of one the same number or one less: where
+// that is odd they take less time, where it is even they cost a few percent (two waves at a block's
+// barriers against four), except in FP64 up to four. Time per LSRK45 stage (us), 256/N_s elements and
+// 256 threads against the choice here: FP64 p=2 343 elements 15.3 / 13.7, p=3 125 14.5 / 12.3,
+// p=4 64 15.9 / 13.3, 512 21.4 / 20.3, 2197 48.5 / 46.9; FP32 form 15.6 / 14.0, 13.0 / 12.4, 14.4 /
+// 13.5, (512: the same), 35.8 / 34.8. Taken further, the choices lose: one element at p=4 1331 30.7 /
+// 32.7, FP32 form 343 16.8 / 17.4, 512 18.1 / 18.6; faces of one wave at p=2 1331 21.1 / 21.6, p=5
+// 512 21.8 / 22.3, FP32 form 20.0 / 20.3; half blocks at p=2 2197 22.3 / 23.6. Beyond the limits
+// half blocks still gain at some sizes (p=2 9261 in the FP32 form 45.2 / 39.1, p=2 4913 33.5 / 32.2):
+// there fr_autotune finds them. Multi-mesh groups keep 256/N_s and 256.
 struct Tiles {
   int epb, fbs;
 };
 inline Tiles tiles_of(const DeviceMesh &dm) {
   if (dm.tiles_set) return {dm.tile_epb, dm.tile_fbs};
   const int whole = tile_elements(dm.Ns, 0), half = tile_elements(dm.Ns, 1);
-  const bool split = half < whole && (dm.Ns == 125 || dm.E <= (int64_t)256 * half);
-  return {split ? 1 : 0, dm.F * dm.Nfp <= 65536 ? 2 : 0};
+  bool split = half < whole && dm.E <= (int64_t)256 * half;
+  if (whole == 2) {
+    const int64_t fullest = (dm.E + 255) / 256;  // elements on the fullest CU, one per block
+    split = fullest % 2 == 1 || (dm.prec == FR_FP64 && fullest <= 4);
+  }
+  return {split ? 1 : 0, dm.F * dm.Nfp <= 32768 ? 2 : 0};
 }
 // The register update of stage s of `scheme` with step dt (st.mode, coefficients) and the state,
 // output and register arrays that stage reads and writes on the handle's buffers.

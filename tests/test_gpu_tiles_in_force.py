@@ -48,3 +48,19 @@ def test_record_of_the_batched_workload(prec):
         assert tuple(m["tiles_alone"]) == g.tiles_in_force() != (0, 0)
         assert tuple(m["tiles"]) == ((0, 0) if prec == "fp32" else g.tiles_in_force())
         g.close()
+
+
+@pytest.mark.parametrize("p,dims,prec,tiles", [
+    # half blocks on at most one per CU, faces of one wave up to 32768 face points
+    (3, (8, 8, 8), "fp64", (1, 2)), (3, (8, 8, 9), "fp64", (0, 2)), (3, (9, 9, 10), "fp64", (0, 0)),
+    (2, (10, 10, 10), "fp32", (1, 2)),
+    (2, (11, 11, 11), "fp32", (0, 0)), (5, (8, 8, 8), "fp32", (0, 0)),
+    # p = 4: one element per block where the fullest CU has an odd number, in FP64 also up to four
+    (4, (6, 6, 7), "fp32", (1, 2)), (4, (8, 8, 8), "fp32", (0, 0)), (4, (8, 8, 9), "fp32", (1, 0)),
+    (4, (8, 8, 8), "fp64", (1, 0)), (4, (11, 11, 11), "fp64", (0, 0)), (4, (13, 13, 13), "fp64", (1, 0))])
+def test_choice_by_size(p, dims, prec, tiles):
+    fr = _fr()
+    kw = dict(prec="fp32", ref_rho=1.0, ref_p=1.0) if prec == "fp32" else {}
+    g = fr.FRMesh(I.box_mesh(dims, q=1), p, mu=1e-3, **kw)
+    assert g.tiles_in_force() == tiles
+    g.close()
