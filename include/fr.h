@@ -161,7 +161,7 @@ int fr_tiles_in_force(fr_mesh_t m, int32_t *epb, int32_t *fbs);
  * fuse = 0 times the stand-alone pre-pass + face + volume kernels and fuse = 1 the face kernel
  * + the volume kernel with the next stage's pre-pass. Allocates two state-sized scratch
  * buffers for the call; waits. The state, the RK registers and the results of later calls are
- * unaffected. */
+ * unaffected. On an error the tiles and the fusion setting stay what they were. */
 int fr_autotune(fr_mesh_t m, int n_trials, double *ms);
 
 /* Stage chaining (default on, both precisions): with on = 1 each RK stage's volume kernel also

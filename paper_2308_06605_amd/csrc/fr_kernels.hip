@@ -1677,6 +1677,8 @@ int fr_autotune(fr_mesh_t m, int n_trials, double *ms) {
   if (hipMemsetAsync(tmp2, 0, M * sizeof(double), s) != hipSuccess) rc = fail(FR_ERR_HIP, "hipMemsetAsync");
   if (rc == FR_OK && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess))
     rc = fail(FR_ERR_HIP, "hipEventCreate");
+  const int epb0 = dm.tile_epb, fbs0 = dm.tile_fbs;
+  const bool set0 = dm.tiles_set;
   dm.tiles_set = true;
   for (int c = 0; c < 12 && rc == FR_OK; ++c) {
     dm.tile_epb = (c % 6) / 3;
@@ -1709,10 +1711,16 @@ int fr_autotune(fr_mesh_t m, int n_trials, double *ms) {
   if (e1) (void)hipEventDestroy(e1);
   (void)hipFree(tmp);
   (void)hipFree(tmp2);
+  if (rc != FR_OK) {  // nothing was chosen: the tiles are what they were
+    dm.tile_epb = epb0;
+    dm.tile_fbs = fbs0;
+    dm.tiles_set = set0;
+    return rc;
+  }
   dm.tile_epb = (bi % 6) / 3;
   dm.tile_fbs = bi % 3;
   dm.fuse = bi >= 6;
-  if (rc == FR_OK && ms)
+  if (ms)
     for (int i = 0; i < 12; ++i) ms[i] = t[i];
   return rc;
 }

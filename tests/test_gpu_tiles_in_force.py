@@ -64,3 +64,23 @@ def test_choice_by_size(p, dims, prec, tiles):
     g = fr.FRMesh(I.box_mesh(dims, q=1), p, mu=1e-3, **kw)
     assert g.tiles_in_force() == tiles
     g.close()
+
+
+@pytest.mark.parametrize("chosen", [None, (1, 1)])
+def test_failed_autotune_chooses_nothing(chosen):
+    """An error left by another HIP call of the thread (a device number out of range) is what the
+    autotuner's first launch check reports: it fails, and the tiles stay by size, or those chosen."""
+    import ctypes
+
+    fr = _fr()
+    g = fr.FRMesh(I.box_mesh(4, q=1), 3, mu=1e-3)
+    if chosen:
+        g.set_tiles(*chosen)
+    before = g.tiles(), g.tiles_in_force(), g.fusion()
+    hip = ctypes.CDLL("libamdhip64.so.7")  # the one the library is linked with
+    assert hip.hipSetDevice(4096) != 0
+    with pytest.raises(fr.FRError):
+        g.autotune(1)
+    hip.hipGetLastError()
+    assert (g.tiles(), g.tiles_in_force(), g.fusion()) == before
+    g.close()
