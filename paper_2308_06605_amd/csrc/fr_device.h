@@ -289,6 +289,8 @@ constexpr bool lds_copy_fits(int bytes, int extra, int threads) {
   return lds_blocks(bytes + extra, threads) == lds_blocks(bytes, threads);
 }
 
+// The 1-D operators as kernel arguments; W, the folded divergence, only in FP64 (the FP32 components
+// keep their traces).
 template <typename real>
 struct OpsT {
   real D[kMaxN * kMaxN];
@@ -296,19 +298,28 @@ struct OpsT {
   real lp[kMaxN];
   real gcL[kMaxN];
   real gcR[kMaxN];
-  real W[kMaxN * kMaxN];
+};
+template <>
+struct OpsT<double> {
+  double D[kMaxN * kMaxN];
+  double lm[kMaxN];
+  double lp[kMaxN];
+  double gcL[kMaxN];
+  double gcR[kMaxN];
+  double W[kMaxN * kMaxN];
 };
 
-// Entry i of the operator entries a volume kernel keeps in LDS: D [N][N], gcL [N], gcR [N],
-// W [N][N] (kOpEntries of them).
+// Entry i of the operator entries a volume kernel keeps in LDS: D [N][N], gcL [N], gcR [N] and, in
+// FP64, W [N][N] (kOpEntries of them).
 template <int N>
 constexpr int kOpEntries = 2 * N * N + 2 * N;
 template <int N, typename real>
 __device__ __forceinline__ real op_entry(const OpsT<real> &ops, int i) {
   const real *tab = reinterpret_cast<const real *>(&ops);
+  constexpr bool HAS_W = sizeof(real) == 8;
   constexpr int oL = kMaxN * kMaxN + 2 * kMaxN, oR = oL + kMaxN, oW = oR + kMaxN;
-  static_assert(sizeof(OpsT<real>) == (oW + kMaxN * kMaxN) * sizeof(real), "the table's members in order");
-  return tab[i < N * N ? i : (i < N * N + N ? oL + i - N * N : (i < N * N + 2 * N ? oR + i - N * N - N : oW + i - N * N - 2 * N))];
+  static_assert(sizeof(OpsT<real>) == (oW + (HAS_W ? kMaxN * kMaxN : 0)) * sizeof(real), "the table's members in order");
+  return tab[i < N * N ? i : (i < N * N + N ? oL + i - N * N : (!HAS_W || i < N * N + 2 * N ? oR + i - N * N - N : oW + i - N * N - 2 * N))];
 }
 
 // Barrier between the LDS phases of an element's threads. Where an element's points fill whole

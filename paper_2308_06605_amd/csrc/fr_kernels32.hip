@@ -771,7 +771,6 @@ void ops_of(const DeviceMesh &dm, OpsT<float> &ops, OpsT<double> &opsd) {
   for (int i = 0; i < kMaxN * kMaxN; ++i) {
     ops.D[i] = float(dm.ops.D[i]);
     opsd.D[i] = dm.ops.D[i];
-    ops.W[i] = float(dm.ops.W[i]);
     opsd.W[i] = dm.ops.W[i];
   }
   for (int i = 0; i < kMaxN; ++i) {
