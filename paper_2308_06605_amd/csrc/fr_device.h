@@ -269,10 +269,11 @@ struct Cfg {
 #ifndef FR_WPE_LDG
 #define FR_WPE_LDG(P) ((P) <= 5 ? 3 : 2)
 #endif
-// The feature kernel at p = 6: left alone the compiler takes 130 VGPRs, two too many for 4 waves
-// (us: 343 elements 13.8 -> 11.0, 729 20.5 -> 17.6, 1728 45.6 -> 38.8).
+// The feature kernel: left alone the compiler takes 130 VGPRs at p = 6, two too many for 4 waves (us:
+// 343 elements 13.8 -> 11.0, 3375 85.7 -> 66.7), and 97 at p = 7, where its LDS allows 6 waves (4096
+// elements 75.8 -> 62.0).
 #ifndef FR_WPE_FEATURES
-#define FR_WPE_FEATURES(P) ((P) == 6 ? 4 : 0)
+#define FR_WPE_FEATURES(P) ((P) == 7 ? 6 : (P) == 6 ? 4 : 0)
 #endif
 #ifndef FR_WPE_VOLUME32
 #define FR_WPE_VOLUME32(P, PRE) ((P) == 7 || ((P) == 5 && !(PRE)) ? 4 : ((P) >= 2 && (PRE) ? 5 : 0))
