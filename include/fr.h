@@ -194,7 +194,9 @@ int fr_rk_step(fr_mesh_t m, double dt, int scheme, int n_steps);
  * solution-point weights w and |J|): out[0] = E_k = sum w|J| |m|^2/(2 rho) / sum w|J|,
  * out[1] = dE_k/dt = sum w|J| (u . R_m - |u|^2 R_rho / 2) / sum w|J| evaluated from the
  * residual R of the handle's precision (one residual is computed). The dissipation rate is
- * -out[1]. The reduction is deterministic (fixed order). Waits for the stream. */
+ * -out[1]. The reduction is deterministic (fixed order). Waits for the stream. Its workspace stays
+ * with the handle and counts in fr_mesh_info's device_bytes: the first RK register (40 N_s bytes per
+ * element; allocated here if no step has needed it yet) and 24 bytes per 256 solution points. */
 int fr_kinetic_energy(fr_mesh_t m, double *out);
 
 /* Sizes of the handle: n_elem, points per element, bytes of device memory held. */
@@ -435,7 +437,7 @@ int fr_mlp_train_step(fr_mlp_t net, const float *X, int64_t n, int64_t ldx, cons
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight training or
  * serving loops, harnesses that forbid hipMalloc): fr_mlp_train_step with the same arguments,
  * kernels and results, bit for bit, but its partial sums of the gradient live in a fixed scratch
- * array (12.3 MiB) that the library holds on each GPU it runs on until the process ends, instead of
+ * array (12.2 MiB) that the library holds on each GPU it runs on until the process ends, instead of
  * a buffer the network grows with hipMalloc. Nothing is
  * allocated or freed. n must be 1..FR_MLP_NOALLOC_MAX_N (FR_ERR_ARG beyond). Every call on one GPU
  * shares that GPU's array and overwrites it: calls that overlap in time on one GPU (other

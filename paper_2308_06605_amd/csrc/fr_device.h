@@ -250,12 +250,16 @@ struct Cfg {
 // Occupancy targets (waves per SIMD) per kernel and degree; 0 lets the compiler decide. From
 // p = 2 on the FP64 volume kernels ask for 4 (at most 128 VGPRs): left alone the compiler takes
 // up to 165 (3 waves; 2 for some) to hoist LDS reads, and the kernels are short of waves, not of
-// loads in flight. They fit without spills, but for 12 bytes per lane at p = 3 and 20 to 28 at
-// p = 6 in the instances without the fused pre-pass. The FP32 form's volume kernel with the
-// fused pre-pass fits 96 VGPRs, 5 waves, at p = 2..6 (13x11x17 p=5 channel: 56.3 -> 52.1 us; 2431
-// blocks then take two rounds of the chip instead of three). Without it 96 spill (36 -> 48 us
-// there), so it asks for 4 at p = 5 and the compiler's choice is 4 elsewhere; at p = 7 a block is
-// eight waves and a fifth wave per SIMD does not fit another.
+// loads in flight. Spills in bytes per lane: BR2 12 at p = 3 without the fused pre-pass, 20 and 28
+// at p = 6 with one element per block (with and without it); LDG 12 at p = 3 without it and at p = 4
+// and 5 with it, 20 and 28 at p = 6; with an eddy viscosity 12 at p = 3 both ways (LDG with it 20),
+// 12 and 20 at p = 6; none elsewhere. The FP32 form's volume kernel with the fused pre-pass asks
+// for 5: it fits 96 VGPRs at p = 2, 4, 5 and 6 (13x11x17 p=5 channel: 56.3 -> 52.1 us; 2431
+// blocks then take two rounds of the chip instead of three; p = 6 with two elements per block
+// spills 12 bytes); at p = 3 the viscous kernel takes 98 and runs 4, which is what its LDS with the
+// metric terms allows. Without the pre-pass 96 spill (36 -> 48 us there), so it asks for 4 at p = 5
+// and the compiler's choice is 4 elsewhere; at p = 7 a block is eight waves and a fifth wave per
+// SIMD does not fit another.
 #ifndef FR_WPE_PREPASS
 #define FR_WPE_PREPASS(P) 0
 #endif
@@ -265,7 +269,9 @@ struct Cfg {
 #ifndef FR_WPE_VOLUME
 #define FR_WPE_VOLUME(P, SGS, PRE) ((P) >= 2 ? 4 : 0)
 #endif
-// The LDG face kernel: 3 is what its LDS allows up to p = 5 (2 above).
+// The LDG face kernel. Its LDS allows 2 waves at p = 1 and 7, 2.5 at p = 3, 3 elsewhere. It asks for
+// 3 up to p = 5 (with an eddy viscosity p = 5 spills 32 bytes per lane) and for 2 above: at p = 6 it
+// takes 150 VGPRs and runs 3, with an eddy viscosity 176 and one block of six waves per CU.
 #ifndef FR_WPE_LDG
 #define FR_WPE_LDG(P) ((P) <= 5 ? 3 : 2)
 #endif
@@ -346,9 +352,11 @@ __device__ __forceinline__ void elem_sync() {
 // p = 2, floats at p = 2 and 4): there consecutive runs share lines, and plain stores let L2
 // merge the pieces (the p = 2 pre-pass 3.56 -> 1.52 ms at 80^3).
 // MERGE: plain stores also for runs longer than a line that end inside one (p = 4, 5, 6). The
-// pre-pass and the face kernels take them: at 52^3 p = 4 FP64 1.14 -> 1.04 ms and 0.98 -> 0.90, at
-// 43^3 p = 5 FP32 form 0.64 -> 0.59 and 0.48 -> 0.47. The fused tail does not: there they measured
-// 1.57 -> 1.62 ms and 1.27 -> 1.28.
+// pre-pass and the BR2 face kernels' interior faces take them: at 52^3 p = 4 FP64 1.14 -> 1.04 ms and
+// 0.98 -> 0.90, at 43^3 p = 5 FP32 form 0.64 -> 0.59 and 0.48 -> 0.47. The fused tail does not: there
+// they measured 1.57 -> 1.62 ms and 1.27 -> 1.28; nor does the LDG face kernel (not measured there).
+// Wall faces and the FP32 form's mass flux are stored non-temporally whatever their runs: one
+// value of ten at most, or the few faces of a wall. Face values at p = 0 and 1: see write_traces.
 template <int NFP, bool MERGE = false, typename T>
 __device__ __forceinline__ void face_store(T v, T *p) {
   constexpr int run = NFP * (int)sizeof(T);

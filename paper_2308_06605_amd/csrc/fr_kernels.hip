@@ -13,8 +13,9 @@
 //              divergence plus the g_DG flux correction, R = -div/|J|, and the RK register
 //              update.
 //
-// The face buffers are written with non-temporal stores: gigabytes that the next kernel
-// reads once, far beyond what the caches would keep (measured: the face kernel 7 % faster).
+// The face buffers are written with non-temporal stores where their runs allow (face_store):
+// gigabytes that the next kernel reads once, far beyond what the caches would keep (measured: the
+// face kernel 7 % faster).
 //
 // Both sides of a face read the same owner-side common flux, so the scheme is exactly
 // conservative. Element data move through LDS; threads map to solution points for volume work
@@ -248,10 +249,12 @@ __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const 
 // Divergence: sum_c D[a][c] F(c) + (F^I_- - F_-) g_L'(a) + (F^I_+ - F_+) g_R'(a), with the traces
 // F_-/+ = sum_c l_c(-/+1) F(c), is sum_c W[a][c] F(c) + F^I_- g_L'(a) + F^I_+ g_R'(a) with
 // W = D - g_L' l(-1)^T - g_R' l(+1)^T. Taken that way it needs no traces: per direction one
-// exchange through LDS instead of three phases (it was 40% of one wave's time at p = 3). Its
-// round-off against long double, on fluxes of a constant plus 10^-3 variations, is 0.7 to 1.2
-// times that of the other form in FP64 and 0.6 to 1.3 times in FP32 over p = 1..7 (rms; the
-// largest error is smaller at all but p = 1 and p = 7, by up to 30%). With the closure (SGS) the
+// exchange through LDS instead of three phases (it was 40% of one wave's time at p = 3). Taken by
+// itself, on fluxes of a constant plus 10^-3 variations, its rms round-off against long double is
+// 0.8 to 1.2 times that of the other form over p = 1..7 (1.2 at p = 2, where its largest error is no
+// larger), and in a residual, where the fluxes' own round-off is most of it, 0.87 to 1.07 times
+// (momentum and energy, 36 curved elements, with and without viscosity; 1.07 in one momentum
+// component at p = 1, 1.03 at most at p = 3, below 1 from p = 4 on). With the closure (SGS) the
 // traces stay: its features take the logarithm of modal energies that vanish by symmetry but for
 // round-off, so that runs to t = 4.5 move by 2e-8 in E_k with any other order of these sums, and
 // the closure's stored evaluation is compared to 1e-8. Each point then takes both traces from the

@@ -563,7 +563,7 @@ namespace {
 
 constexpr int64_t kNoAllocMaxN = FR_MLP_NOALLOC_MAX_N;
 constexpr int64_t kMaxParams = (int64_t)H * kMaxIn + H + H * H + H + H + 1;
-constexpr int64_t kScratchFloats = train_parts(kNoAllocMaxN) * (kMaxParams + 1);  // 12.3 MiB
+constexpr int64_t kScratchFloats = train_parts(kNoAllocMaxN) * (kMaxParams + 1);  // 12.2 MiB
 
 }  // namespace
 
