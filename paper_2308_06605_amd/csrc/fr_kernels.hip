@@ -252,9 +252,9 @@ __global__ __launch_bounds__(FBS) FR_WPE_ATTR(FR_WPE_FACE(P)) void k_face(const 
 // exchange through LDS instead of three phases (it was 40% of one wave's time at p = 3). Taken by
 // itself, on fluxes of a constant plus 10^-3 variations, its rms round-off against long double is
 // 0.8 to 1.2 times that of the other form over p = 1..7 (1.2 at p = 2, where its largest error is no
-// larger), and in a residual, where the fluxes' own round-off is most of it, 0.87 to 1.07 times
-// (momentum and energy, 36 curved elements, with and without viscosity; 1.07 in one momentum
-// component at p = 1, 1.03 at most at p = 3, below 1 from p = 4 on). With the closure (SGS) the
+// larger). In a viscous residual, where the fluxes' own round-off is most of it, it is 0.95 to 1.01
+// times that of before at p = 1..3 (any variable; 120 curved elements, eight states) and 0.87 to 1.00
+// above (36 elements, three states). With the closure (SGS) the
 // traces stay: its features take the logarithm of modal energies that vanish by symmetry but for
 // round-off, so that runs to t = 4.5 move by 2e-8 in E_k with any other order of these sums, and
 // the closure's stored evaluation is compared to 1e-8. Each point then takes both traces from the
